@@ -1,0 +1,43 @@
+"""Escape-time counts where the blocked loop, its escape test and its cycle
+test could go wrong: caps around the block length, |c| near 2 (the plain
+loop's border, the tip of the real axis and c = -2, whose orbit is a cycle),
+components of c near the smallest it scales, zero, denormal, huge and NaN
+coordinates. Counts are whole numbers and equal the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1805_02755_amd as ce
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+# (x0, y0, dx, dy)
+REGIONS = {
+    "set": (-2.0, -1.5, 3.0 / 128, 3.0 / 96),
+    "tip": (-2.0, -2e-5, 1e-6, 1e-6),
+    "tip_outside": (-2.00001, 0.0, 2.4e-7, 1e-6),
+    "circle": (1.3, 1.3, 0.002, 0.002),
+    "border_of_plain": (-1.99999, -0.02, 1e-7, 5e-4),
+    "seahorse": (-0.75, 0.1, 2e-4, 2e-4),
+    "near_zero": (-2e-6, -2e-6, 4e-8, 4e-8),
+    "zero_row": (-2.0, 0.0, 3.0 / 128, 0.0),
+    "zero_column": (0.0, -1.5, 0.0, 3.0 / 96),
+    "least_imaginary": (-1.9, -4e-18, 0.01, 1e-19),
+    "denormal_imaginary": (-1.9, 0.0, 0.01, 1e-40),
+    "tiny_real": (0.0, 0.3, 1e-38, 0.01),
+    "huge": (-1e30, -1e38, 1e28, 3e36),
+    "nan": (float("nan"), -1.0, 0.01, 0.02),
+}
+
+
+@pytest.mark.parametrize("max_iter", [1, 2, 7, 8, 9, 16, 17, 100, 1003])
+@pytest.mark.parametrize("region", sorted(REGIONS))
+def test_counts_equal_the_oracles(region, max_iter):
+    w, h = 131, 96
+    x0, y0, dx, dy = (float(np.float32(v)) for v in REGIONS[region])
+    out = torch.full((h, w), -1, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    ce.ce_bare_run(ce.CE_KERNEL_ESCAPE, ce.ce_escape_params(w, h, x0, y0, dx, dy, max_iter), [], out)
+    ref = O.escape(w, h, x0, y0, dx, dy, max_iter)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
