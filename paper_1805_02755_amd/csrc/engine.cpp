@@ -1563,6 +1563,10 @@ struct ce_engine {
         if (light_exit && fast_g1 > fast_g0 && !v.empty()) {
           v[0].g0 = fast_g0;
           v[0].g1 = fast_g1;
+          // Its claim tick is the first workgroup's start, which may come
+          // after another workgroup has run a package of short tiles to its
+          // end (the XCDs start about a microsecond apart): it began by then.
+          v[0].t_claim = std::min(v[0].t_claim, v[0].t_end);
         }
         for (auto& p : v)
           trace.push_back(ce_package_rec{(uint32_t)gi, 0, p.g0, p.g1, tick_to_host_s(p.t_claim), tick_to_host_s(p.t_end)});
