@@ -12,6 +12,14 @@
 
 namespace ce {
 
+// This thread's index, opaque to the compiler: what a tile works out from it
+// is otherwise kept in registers over the tile loop, which has none to spare.
+__device__ __forceinline__ uint32_t thread_index() {
+  uint32_t t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 struct EscapeTile {
   // workgroups per CU the persistent kernel is compiled for: eight, the
   // residency of the plain launch, so that the 2048 tiles of a 1024 x 1024
@@ -206,8 +214,9 @@ struct Blur5TileT {
     const uint64_t r0 = g0 + (uint64_t)(t / nc) * kBlurTileRows;
     const uint64_t r1 = (r0 + kBlurTileRows < g1) ? r0 + kBlurTileRows : g1;
     // first column of this wave (uniform) and of this lane
-    const uint32_t xw = (t % nc) * kBlurTileCols + (__builtin_amdgcn_readfirstlane(threadIdx.x) & ~63u) * 4u;
-    const uint32_t x = xw + (threadIdx.x & 63u) * 4u;
+    const uint32_t tid = thread_index();
+    const uint32_t xw = (t % nc) * kBlurTileCols + (__builtin_amdgcn_readfirstlane(tid) & ~63u) * 4u;
+    const uint32_t x = xw + (tid & 63u) * 4u;
     if (xw >= p.w) return;
     if ((p.w & 3u) == 0 && xw + 256 <= p.w)
       run_fast(r0, r1, x, xw);
@@ -219,111 +228,268 @@ struct Blur5TileT {
 using Blur5Tile = Blur5TileT<false>;
 using Blur5TileFresh = Blur5TileT<true>;
 
-// Lomont, "Fast Inverse Square Root" (2003): integer estimate then three
-// Newton-Raphson steps y <- y (1.5 - (x/2) y^2) written as t = y*y,
-// u = fma(-(x/2), t, 1.5), y = y*u. Same operation sequence as the host.
-__device__ __forceinline__ float rsqrt_lomont(float x) {
-  const uint32_t b = 0x5f375a86u - (__float_as_uint(x) >> 1);
-  float y = __uint_as_float(b);
-  const float hx = 0.5f * x;
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const float t = y * y;
-    const float u = __builtin_fmaf(-hx, t, 1.5f);
-    y = y * u;
-  }
-  return y;
-}
-
 // All-pairs acceleration of body i (NBody program, force part): the sum of
 // m_j d_ij / (|d_ij|^2 + eps2)^(3/2) over j ascending, one FP32 sum per
-// component. Positions of the j bodies are staged through LDS 256 at a time;
-// every thread of the workgroup takes part in the staging, and loads its
-// part of the next stage while the current one is computed (at 65,536
-// bodies a workgroup is one wave per SIMD, so no other wave hides that
-// load). Eight bodies per step: measured against 4 and 16, and against
-// reading the next eight from LDS during the current eight, it is fastest.
+// component.
+//
+// The order of a body's sum is fixed, but only three of an interaction's 24
+// instructions are the sum. So a group of 64 bodies, one per lane, is worked
+// on by all the waves of a workgroup: wave w takes the chunks w, w + kWaves,
+// ... of kChunk consecutive j, works out a chunk's terms (f, dx, dy, dz) in
+// registers, waits until the chunk before has been added, adds its own in
+// index order and hands the sums on through LDS (`turn` counts the chunks
+// added). With one thread per body the GPU held 1024 waves at 65,536 bodies,
+// one per SIMD, and a SIMD issues the FP32 instructions of one wave only
+// every 5.1 cycles where two or four waves reach 2.6; and below 65,536 bodies
+// most SIMDs were idle.
+//
+// A wave stages its own chunks in LDS (two slots; a chunk is loaded a turn
+// before it is needed) and reads them in batches of eight bodies, each batch
+// a phase ahead of its arithmetic. LDS operations of one wave take effect in
+// order, so a reader that sees `turn` sees the sums stored before it.
+constexpr uint32_t kNbodyGroup = 64;  // bodies per tile: one per lane
+constexpr uint32_t kNbodyBatch = 8;
+constexpr uint32_t kNbodyChunk = 24;  // of a 256-thread workgroup: 128 registers, four waves per SIMD
+
+template <uint32_t kWaves, uint32_t kChunk>
+struct NbodyShared {
+  f32x4 stage[kWaves][2][kChunk];
+  f32x4 sum[kNbodyGroup];
+  uint32_t turn;
+};
+
+// A zero that the compiler does not keep in registers over the tile loop.
+__device__ __forceinline__ float fresh_zero() {
+  float x = 0.0f;
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 template <bool STRICT>
-__device__ __forceinline__ void nbody_accumulate(const float4* pos, uint32_t n, float eps2, const float4 pi,
-                                                 float4* sh, float& ax, float& ay, float& az) {
-  ax = 0.0f;
-  ay = 0.0f;
-  az = 0.0f;
-  float4 stage = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (threadIdx.x < n) stage = pos[threadIdx.x];
-  for (uint32_t j0 = 0; j0 < n; j0 += kNbodyGranule) {
+struct NbodyTerms {
+  float eps2;
+  // Lomont, "Fast Inverse Square Root" (2003): integer estimate then three
+  // Newton-Raphson steps y <- y (1.5 - (x/2) y^2) written as t = y*y,
+  // u = fma(-(x/2), t, 1.5), y = y*u. Same operation sequence as the host.
+  __device__ __forceinline__ float rsqrt_lomont(float x) const {
+    float y = __uint_as_float(0x5f375a86u - (__float_as_uint(x) >> 1));
+    const float hx = 0.5f * x;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const float t = y * y;
+      const float u = __builtin_fmaf(-hx, t, 1.5f);
+      y = y * u;
+    }
+    return y;
+  }
+  // (dx, dy, dz, f) of body pj = (x, y, z, m) as seen from pi
+  __device__ __forceinline__ f32x4 operator()(const f32x4 pj, const f32x4 pi) const {
+    const float dx = pj.x - pi.x;
+    const float dy = pj.y - pi.y;
+    const float dz = pj.z - pi.z;
+    const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
+    const float rinv = STRICT ? rsqrt_lomont(r2) : __builtin_amdgcn_rsqf(r2);
+    const float s = (rinv * rinv) * rinv;
+    return f32x4{dx, dy, dz, pj.w * s};
+  }
+};
+
+__device__ __forceinline__ void nbody_add(f32x4& a, const f32x4 t) {
+  a.x = __builtin_fmaf(t.w, t.x, a.x);
+  a.y = __builtin_fmaf(t.w, t.y, a.y);
+  a.z = __builtin_fmaf(t.w, t.z, a.z);
+}
+
+// The acceleration of this lane's body pi. Every wave of the workgroup takes
+// part; true in the one wave that returns the sums.
+template <bool STRICT, uint32_t kWaves, uint32_t kChunk>
+__device__ __forceinline__ bool nbody_accumulate(const f32x4* pos, uint32_t n, float eps2, uint32_t lane,
+                                                 const f32x4 pi, NbodyShared<kWaves, kChunk>& sh, f32x4& acc) {
+  static_assert(kChunk % kNbodyBatch == 0 && kChunk <= 64, "whole batches, one body per lane to stage");
+  const NbodyTerms<STRICT> terms{eps2};
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t chunks = n / kChunk;  // whole ones
+  f32x4(*const slot)[kChunk] = sh.stage[w];
+  // Every wait ends: chunk c is added by a wave of this workgroup, which
+  // waits only for the chunks before it.
+  const auto sums_at = [&](uint32_t c) {
+    while ((uint32_t)__builtin_amdgcn_readfirstlane(
+               __hip_atomic_load(&sh.turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != c) {
+    }
+    asm volatile("" ::: "memory");
+    return sh.sum[lane];
+  };
+  __syncthreads();  // the tile before is done with `sh`
+  if (w == 0) {
+    const float zero = fresh_zero();
+    sh.sum[lane] = f32x4{zero, zero, zero, zero};
+    if (lane == 0) sh.turn = 0;
+  }
+  if (lane < kChunk && w < chunks) slot[0][lane] = pos[w * kChunk + lane];
+  __syncthreads();
+  f32x4 t[kChunk], next = pi;  // any value: a lane or turn that does not load does not use it
+  uint32_t s = 0;
+  for (uint32_t c = w; c < chunks; c += kWaves) {
+    // two batches, then one more ahead of each batch's arithmetic
+#pragma unroll
+    for (uint32_t k = 0; k < 2 * kNbodyBatch && k < kChunk; ++k) t[k] = slot[s][k];
+    if (lane < kChunk && c + kWaves < chunks) next = pos[(c + kWaves) * kChunk + lane];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (uint32_t q = 0; q < kChunk; q += kNbodyBatch) {
+      if (q > 0 && q + kNbodyBatch < kChunk) {
+#pragma unroll
+        for (uint32_t k = q + kNbodyBatch; k < q + 2 * kNbodyBatch; ++k) t[k] = slot[s][k];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // A few bodies interleaved at a time (all eight would spill), and
+      // worked out here: without the fences the compiler moves the arithmetic
+      // past the wait below. Two bodies hide the latency of an instruction
+      // with four waves per SIMD, four with two.
+      constexpr uint32_t kTogether = kWaves > 4 ? 4 : 2;
+#pragma unroll
+      for (uint32_t k0 = q; k0 < q + kNbodyBatch; k0 += kTogether) {
+#pragma unroll
+        for (uint32_t k = k0; k < k0 + kTogether; ++k) t[k] = terms(t[k], pi);
+#pragma unroll
+        for (uint32_t k = k0; k < k0 + kTogether; ++k) asm volatile("" : "+v"(t[k]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    acc = sums_at(c);
+    __builtin_amdgcn_s_setprio(3);  // the other waves wait for this chain
+#pragma unroll
+    for (uint32_t k = 0; k < kChunk; ++k) nbody_add(acc, t[k]);
+    sh.sum[lane] = acc;
+    asm volatile("" ::: "memory");
+    __hip_atomic_store(&sh.turn, c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_s_setprio(0);
+    s ^= 1u;
+    if (lane < kChunk) slot[s][lane] = next;
+  }
+  if (w != chunks % kWaves) return false;
+  // the bodies past the last whole chunk, and the result
+  const uint32_t j0 = chunks * kChunk, m = n - j0;
+  if (lane < m) slot[0][lane] = pos[j0 + lane];
+  acc = sums_at(chunks);
+#pragma unroll 1
+  for (uint32_t k = 0; k < m; ++k) nbody_add(acc, terms(slot[0][k], pi));
+  return true;
+}
+
+// The same acceleration with one thread per body: a tile of 256 bodies, each
+// j read from LDS by all four waves, staged 256 at a time; every thread of the
+// workgroup takes part in the staging, and loads its part of the next stage
+// while the current one is computed. Two batches of eight bodies in
+// registers: the next batch is read from LDS while the current one is
+// computed (scheduling fences keep each batch's reads a phase ahead of its
+// arithmetic). Nothing is handed on, so it is the faster form where it
+// alone gives every SIMD two or four waves.
+constexpr uint32_t kNbodyWhole = 256;
+
+template <bool STRICT>
+__device__ __forceinline__ f32x4 nbody_accumulate_whole(const f32x4* pos, uint32_t n, float eps2, uint32_t tid,
+                                                        const f32x4 pi, f32x4 (&sh)[kNbodyWhole]) {
+  const NbodyTerms<STRICT> terms{eps2};
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f}, stage = pi;
+  if (tid < n) stage = pos[tid];
+  for (uint32_t j0 = 0; j0 < n; j0 += kNbodyWhole) {
     __syncthreads();
-    sh[threadIdx.x] = stage;
+    sh[tid] = stage;
     __syncthreads();
-    if (j0 + kNbodyGranule + threadIdx.x < n) stage = pos[j0 + kNbodyGranule + threadIdx.x];
-    const uint32_t m = (n - j0 < kNbodyGranule) ? n - j0 : kNbodyGranule;
-    const auto body = [&](const float4 pj) {
-      const float dx = pj.x - pi.x;
-      const float dy = pj.y - pi.y;
-      const float dz = pj.z - pi.z;
-      const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
-      const float rinv = STRICT ? rsqrt_lomont(r2) : __builtin_amdgcn_rsqf(r2);
-      const float s = (rinv * rinv) * rinv;
-      const float f = pj.w * s;
-      ax = __builtin_fmaf(f, dx, ax);
-      ay = __builtin_fmaf(f, dy, ay);
-      az = __builtin_fmaf(f, dz, az);
-    };
-    // Two batches of eight bodies in registers: the next batch is read from
-    // LDS while the current one is computed, so the reads' latency never
-    // waits on the arithmetic (with one wave per SIMD nothing else would
-    // hide it, and how much of it a plain unrolled loop hides depends on the
-    // compiler's schedule). Scheduling fences keep each batch's reads a
-    // phase ahead of its arithmetic; the bodies of a batch still interleave.
-    // The bodies are taken in index order.
+    if (j0 + kNbodyWhole + tid < n) stage = pos[j0 + kNbodyWhole + tid];
+    const uint32_t m = (n - j0 < kNbodyWhole) ? n - j0 : kNbodyWhole;
     uint32_t jj = 0;
-    if (m >= 8) {
-      float4 a[8], b[8];
+    if (m >= kNbodyBatch) {
+      f32x4 a[kNbodyBatch], b[kNbodyBatch];
 #pragma unroll
-      for (uint32_t k = 0; k < 8; ++k) a[k] = sh[k];
-      for (; jj + 16 <= m; jj += 16) {
+      for (uint32_t k = 0; k < kNbodyBatch; ++k) a[k] = sh[k];
+      for (; jj + 2 * kNbodyBatch <= m; jj += 2 * kNbodyBatch) {
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) b[k] = sh[jj + 8 + k];
+        for (uint32_t k = 0; k < kNbodyBatch; ++k) b[k] = sh[jj + kNbodyBatch + k];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) body(a[k]);
+        for (uint32_t k = 0; k < kNbodyBatch; ++k) nbody_add(acc, terms(a[k], pi));
         __builtin_amdgcn_sched_barrier(0);
         // the batch after (read within the stage; unused past its end)
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) a[k] = sh[(jj + 16 + k) & (kNbodyGranule - 1)];
+        for (uint32_t k = 0; k < kNbodyBatch; ++k) a[k] = sh[(jj + 2 * kNbodyBatch + k) & (kNbodyWhole - 1)];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) body(b[k]);
+        for (uint32_t k = 0; k < kNbodyBatch; ++k) nbody_add(acc, terms(b[k], pi));
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (jj + 8 <= m) {
+      if (jj + kNbodyBatch <= m) {
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) body(a[k]);
-        jj += 8;
+        for (uint32_t k = 0; k < kNbodyBatch; ++k) nbody_add(acc, terms(a[k], pi));
+        jj += kNbodyBatch;
       }
     }
-    for (; jj < m; ++jj) body(sh[jj]);
+    for (; jj < m; ++jj) nbody_add(acc, terms(sh[jj], pi));
   }
+  return acc;
 }
 
-// Accelerations: a granule is 256 bodies, one per thread.
+// Whether the engine's tiles are whole granules: with the strict 1/sqrt, where
+// the granules give (nearly) every one of the 256 compute units two, so two
+// waves per SIMD. At 131,072 bodies 6.88 ms against 7.35 in groups of 64, at
+// 122,880 6.26 against 6.77; with one and a half waves per SIMD (98,304) it is
+// 4.76 against 4.16, with three (196,608) 19.1 against 16.3, with four 28.5
+// against 28.3. With the hardware 1/sqrt the groups are always faster
+// (131,072: 5.26 against 5.63).
+template <bool STRICT>
+__host__ __device__ inline bool nbody_whole(uint32_t n) {
+  const uint32_t granules = n / kNbodyGranule + (n % kNbodyGranule != 0);
+  return STRICT && granules > 464 && granules <= 512;
+}
+
+// Tiles of a range of 256-body granules in groups of 64 bodies.
+__host__ __device__ inline uint32_t nbody_tiles(uint32_t n, uint64_t g0, uint64_t g1) {
+  const uint64_t end = g1 * kNbodyGranule < n ? g1 * kNbodyGranule : n;
+  return g0 * kNbodyGranule < end ? (uint32_t)ceil_div(end - g0 * kNbodyGranule, kNbodyGroup) : 0;
+}
+
+// Accelerations: a granule is 256 bodies, a tile 64 of them or all.
 template <bool STRICT>
 struct NbodyTile {
-  static constexpr int kMinBlocksPerCu = 1;  // one granule per workgroup: no bound
+  // four workgroups per CU: four waves per SIMD, 128 registers each
+  static constexpr int kMinBlocksPerCu = 4;
   ce_nbody_params p;
   const float4* pos;
   float4* out;
   __device__ void load_constants() {}
   __host__ __device__ uint64_t granules() const { return ceil_div(p.n, kNbodyGranule); }
-  __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const { return (uint32_t)(g1 - g0); }
+  __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
+    return nbody_whole<STRICT>(p.n) ? (uint32_t)(g1 - g0) : nbody_tiles(p.n, g0, g1);
+  }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    __shared__ float4 sh[kNbodyGranule];
-    const uint64_t i = (g0 + t) * kNbodyGranule + threadIdx.x;
+    if (STRICT && nbody_whole<STRICT>(p.n))
+      run_whole(g0, t);
+    else
+      run_group<kBlockThreads / 64, kNbodyChunk>(g0, t);
+  }
+  template <uint32_t kWaves, uint32_t kChunk>
+  __device__ __forceinline__ void run_group(uint64_t g0, uint32_t t) const {
+    __shared__ NbodyShared<kWaves, kChunk> sh;
+    const uint32_t lane = thread_index() & 63u;
+    const uint64_t i = g0 * kNbodyGranule + (uint64_t)t * kNbodyGroup + lane;
     const bool active = i < p.n;
-    const float4 pi = active ? pos[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    float ax, ay, az;
-    nbody_accumulate<STRICT>(pos, p.n, p.eps2, pi, sh, ax, ay, az);
-    if (active) out[i] = make_float4(ax, ay, az, 0.0f);
+    const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
+    const f32x4 pi = active ? p4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 a;
+    if (nbody_accumulate<STRICT, kWaves, kChunk>(p4, p.n, p.eps2, lane, pi, sh, a) && active) store(i, a);
+  }
+  __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
+    __shared__ f32x4 sh[kNbodyWhole];
+    const uint32_t tid = thread_index();
+    const uint64_t i = (g0 + t) * kNbodyGranule + tid;
+    const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
+    const f32x4 pi = i < p.n ? p4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4 a = nbody_accumulate_whole<STRICT>(p4, p.n, p.eps2, tid, pi, sh);
+    if (i < p.n) store((g0 + t) * kNbodyGranule + thread_index(), a);
+  }
+  __device__ __forceinline__ void store(uint64_t i, const f32x4 a) const {
+    out[i] = make_float4(a.x, a.y, a.z, 0.0f);
   }
 };
 
@@ -333,7 +499,7 @@ struct NbodyTile {
 // the mass and the velocity's w are copied.
 template <bool STRICT>
 struct NbodyStepTile {
-  static constexpr int kMinBlocksPerCu = 1;
+  static constexpr int kMinBlocksPerCu = 4;
   ce_nbody_step_params p;
   const float4* pos;
   const float4* vel;
@@ -341,26 +507,47 @@ struct NbodyStepTile {
   float4* vel_out;
   __device__ void load_constants() {}
   __host__ __device__ uint64_t granules() const { return ceil_div(p.n, kNbodyGranule); }
-  __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const { return (uint32_t)(g1 - g0); }
+  __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
+    return nbody_whole<STRICT>(p.n) ? (uint32_t)(g1 - g0) : nbody_tiles(p.n, g0, g1);
+  }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    __shared__ float4 sh[kNbodyGranule];
-    const uint64_t i = (g0 + t) * kNbodyGranule + threadIdx.x;
+    if (STRICT && nbody_whole<STRICT>(p.n))
+      run_whole(g0, t);
+    else
+      run_group<kBlockThreads / 64, kNbodyChunk>(g0, t);
+  }
+  template <uint32_t kWaves, uint32_t kChunk>
+  __device__ __forceinline__ void run_group(uint64_t g0, uint32_t t) const {
+    __shared__ NbodyShared<kWaves, kChunk> sh;
+    const uint32_t lane = thread_index() & 63u;
+    const uint64_t i = g0 * kNbodyGranule + (uint64_t)t * kNbodyGroup + lane;
     const bool active = i < p.n;
-    const float4 pi = active ? pos[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    float ax, ay, az;
-    nbody_accumulate<STRICT>(pos, p.n, p.eps2, pi, sh, ax, ay, az);
-    if (!active) return;
+    const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
+    const f32x4 pi = active ? p4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 a;
+    if (nbody_accumulate<STRICT, kWaves, kChunk>(p4, p.n, p.eps2, lane, pi, sh, a) && active) store(i, pi, a);
+  }
+  __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
+    __shared__ f32x4 sh[kNbodyWhole];
+    const uint32_t tid = thread_index();
+    const uint64_t i = (g0 + t) * kNbodyGranule + tid;
+    const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
+    const f32x4 pi = i < p.n ? p4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4 a = nbody_accumulate_whole<STRICT>(p4, p.n, p.eps2, tid, pi, sh);
+    if (i < p.n) store((g0 + t) * kNbodyGranule + thread_index(), pi, a);
+  }
+  __device__ __forceinline__ void store(uint64_t i, const f32x4 pi, const f32x4 a) const {
     const float4 vi = vel[i];
     const float dt = p.dt;
     const float h = (dt * dt) * 0.5f;
     float4 xo, vo;
-    xo.x = (pi.x + vi.x * dt) + ax * h;
-    xo.y = (pi.y + vi.y * dt) + ay * h;
-    xo.z = (pi.z + vi.z * dt) + az * h;
+    xo.x = (pi.x + vi.x * dt) + a.x * h;
+    xo.y = (pi.y + vi.y * dt) + a.y * h;
+    xo.z = (pi.z + vi.z * dt) + a.z * h;
     xo.w = pi.w;
-    vo.x = vi.x + ax * dt;
-    vo.y = vi.y + ay * dt;
-    vo.z = vi.z + az * dt;
+    vo.x = vi.x + a.x * dt;
+    vo.y = vi.y + a.y * dt;
+    vo.z = vi.z + a.z * dt;
     vo.w = vi.w;
     pos_out[i] = xo;
     vel_out[i] = vo;

@@ -16,6 +16,15 @@ namespace ce {
 __device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
 // ---------------------------------------------------------------- dispenser
+// The "no more packages" flag as a value the compiler cannot see through: it
+// would otherwise keep the constant in a register pair over the tile loop,
+// where some payloads have none to spare.
+__device__ __forceinline__ uint64_t done_flag() {
+  uint32_t hi = (uint32_t)(kTotalDone >> 32);
+  asm volatile("" : "+v"(hi));
+  return (uint64_t)hi << 32;
+}
+
 // Bounded waits: true once more than `limit` ticks have passed since the
 // first call with *t0 == 0 (which starts the clock). Every wait in the
 // dispenser ends this way, well before the host gives up on the kernel.
@@ -236,7 +245,7 @@ __device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t*
         const uint32_t pre = s.pre_nt ? 1u : 0u;
         if (dev_load(&q->n_pkgs) + pre >= s.max_pkgs || !claim_package(s, &g0, &g1, &timed_out)) {
           if (timed_out || dev_load(&q->n_pkgs) + pre >= s.max_pkgs) sys_store(&s.l1->gpu_flags, 1);
-          dev_store(&q->total, tot2 | kTotalDone);
+          dev_store(&q->total, tot2 | done_flag());
         } else if (s.kind == kDynamic) {
           publish_dynamic(pay, s, tot2, g0, g1, tc);
         } else {
@@ -258,7 +267,7 @@ __device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t*
     ++spins;
     if (waited_out(&t0, s.wait_ticks)) {
       sys_store(&s.l1->gpu_flags, 1);
-      __hip_atomic_fetch_or(&q->total, kTotalDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_or(&q->total, done_flag(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __builtin_amdgcn_s_waitcnt(0);  // done before this workgroup counts out and the state is reset
       return false;
     }

@@ -20,6 +20,24 @@ namespace {
 
 constexpr uint32_t kDescWords = sizeof(ServeDesc) / 8;
 
+// N-body jobs of fewer bodies than this run in groups of 64 bodies, so that a
+// job alone on the GPU uses more than a few compute units; larger ones with
+// one thread per body, which takes fewer instructions when the GPU is full.
+// The groups' chunks are shorter than the engine's, which would leave the
+// kernel four workgroups per compute unit instead of five.
+constexpr uint32_t kServeWholeBodies = 32768;
+constexpr uint32_t kServeNbodyChunk = 8;
+
+template <bool STRICT>
+__device__ void serve_nbody(const ServeDesc& d, uint32_t ti) {
+  const ce_nbody_params nb{(uint32_t)__builtin_amdgcn_readfirstlane(d.nb.n), d.nb.eps2, d.nb.strict};
+  const NbodyTile<STRICT> t{nb, (const float4*)d.in0, (float4*)d.out};
+  if (nb.n >= kServeWholeBodies)  // uniform: both forms hold barriers
+    t.run_whole(0, ti);
+  else
+    t.template run_group<kBlockThreads / 64, kServeNbodyChunk>(0, ti);
+}
+
 __device__ __forceinline__ uint64_t sys_load_c(const uint64_t* p) { return sys_load(const_cast<uint64_t*>(p)); }
 
 // Takes the next tile ticket; returns false when the session is over (the
@@ -113,17 +131,15 @@ __device__ void serve_tile(const ServeDesc& d, uint32_t ti) {
     b.load_constants();
     b.run(0, d.granules, ti);
   } else if (__builtin_amdgcn_readfirstlane(d.strict)) {
-    NbodyTile<true> nbt{d.nb, (const float4*)d.in0, (float4*)d.out};
-    nbt.run(0, d.granules, ti);
+    serve_nbody<true>(d, ti);
   } else {
-    NbodyTile<false> nbt{d.nb, (const float4*)d.in0, (float4*)d.out};
-    nbt.run(0, d.granules, ti);
+    serve_nbody<false>(d, ti);
   }
 }
 
 }  // namespace
 
-__global__ __launch_bounds__(kBlockThreads) void k_serve(ServeArgs a) {
+__global__ __launch_bounds__(kBlockThreads, 5) void k_serve(ServeArgs a) {
   __shared__ ServeDesc sh_desc;
   __shared__ uint32_t sh_go, sh_job, sh_ti, sh_nt;
   const bool wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x) == 0;
@@ -190,7 +206,9 @@ uint32_t serve_tiles(const ServeDesc& d) {
   switch (d.kind) {
     case CE_KERNEL_ESCAPE: return EscapeTile{d.esc, nullptr}.ntiles(0, d.esc.h);
     case CE_KERNEL_BLUR5: return Blur5Tile{d.blur, nullptr, nullptr, nullptr, {}}.ntiles(0, d.blur.h);
-    case CE_KERNEL_NBODY_ACC: return (uint32_t)ceil_div(d.nb.n, kNbodyGranule);
+    case CE_KERNEL_NBODY_ACC:
+      return d.nb.n >= kServeWholeBodies ? (uint32_t)ceil_div(d.nb.n, kNbodyGranule)
+                                         : nbody_tiles(d.nb.n, 0, ceil_div(d.nb.n, kNbodyGranule));
   }
   return 0;
 }

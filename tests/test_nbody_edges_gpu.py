@@ -1,0 +1,101 @@
+"""N-body sizes where the handing-on of the sums could go wrong: around a chunk
+(8, 24, 48 bodies), a round of chunks over a workgroup's waves, a group of 64
+bodies, a granule, and the borders between the forms (wide groups, groups,
+whole granules); in the direct, persistent, plain and serving kernels. The
+strict form equals the oracle bit for bit; the hardware 1/sqrt lies within
+1e-5 of the sum of the terms' lengths."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1805_02755_amd as ce
+from paper_1805_02755_amd import synth
+from oracle import oracle as O
+
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+EPS2 = 1e-6
+SIZES = [1, 2, 7, 8, 9, 23, 24, 25, 47, 48, 49, 63, 64, 65, 95, 96, 97, 191, 192, 193, 255, 256, 257, 383, 384, 385,
+         767, 768, 769, 1000]
+BORDERS = [16384, 16385, 32767, 32768, 118784, 118785, 131072, 131073]
+
+
+@pytest.fixture(scope="module")
+def eng():
+    e = ce.Engine()
+    yield e
+    e.close()
+
+
+def forms(eng, pos, strict, which):
+    """(name, output) of the acceleration in each form of the kernel."""
+    n = pos.shape[0]
+    p_d = torch.from_numpy(pos).to(DEV)
+    prm = ce.ce_nbody_params(n, EPS2, strict)
+    out = torch.full((n, 4), float("nan"), device=DEV)
+    torch.cuda.synchronize()
+    if "plain" in which:
+        ce.ce_bare_run(ce.CE_KERNEL_NBODY_ACC, prm, [p_d], out)
+        yield "plain", out.cpu().numpy()
+    for name, sched in (("direct", dict(kind=ce.CE_SCHED_STATIC)),
+                        ("persistent", dict(kind=ce.CE_SCHED_DYNAMIC, package_granules=1))):
+        if name not in which:
+            continue
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        eng.use(ce.CE_DEV_GPU, 0, 0)
+        eng.work_items([n], [256])
+        eng.scheduler(**sched)
+        eng.program_kernel(ce.CE_KERNEL_NBODY_ACC, prm)
+        eng.program_in(0, dev=p_d, nbytes=n * 16)
+        eng.program_out(0, dev=out, nbytes=n * 16)
+        eng.run()
+        yield name, out.cpu().numpy()
+    if "serve" in which:
+        with ce.Server(64 << 20, keep_outputs=True, session_timeout_s=30.0) as srv:
+            t = srv.submit(ce.CE_KERNEL_NBODY_ACC, prm, p_d)
+            srv.wait(t, 60.0)
+            res = np.empty((n, 4), np.float32)
+            srv.copy_output(t, res)
+            srv.drain(60.0)
+        yield "serve", res
+
+
+def same(a, b):
+    return np.array_equal(np.ascontiguousarray(a).view(np.uint32), np.ascontiguousarray(b).view(np.uint32))
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_small_sizes_every_body(eng, n):
+    pos = synth.nbody_bodies(n, seed=1000 + n)
+    ref = O.nbody_acc(pos, EPS2, True)
+    for name, out in forms(eng, pos, 1, ("plain", "direct", "persistent")):
+        assert same(out, ref), (name, n)
+    if n > 1:
+        ref64 = O.nbody_acc_f64(pos, EPS2)
+        for name, out in forms(eng, pos, 0, ("plain", "direct", "persistent")):
+            d = pos[None, :, :3].astype(np.float64) - pos[:, None, :3]
+            r2 = (d * d).sum(-1) + np.float64(np.float32(EPS2))
+            bound = 1e-5 * (pos[None, :, 3] * np.sqrt((d * d).sum(-1)) * r2 ** -1.5).sum(1)
+            assert np.all(np.linalg.norm(out[:, :3] - ref64[:, :3], axis=1) <= bound), (name, n)
+
+
+def test_serving_sizes(eng):
+    for n in (1, 9, 65, 385, 1000):
+        pos = synth.nbody_bodies(n, seed=2000 + n)
+        ref = O.nbody_acc(pos, EPS2, True)
+        for name, out in forms(eng, pos, 1, ("serve",)):
+            assert same(out, ref), (name, n)
+
+
+@pytest.mark.parametrize("n", BORDERS)
+def test_borders_between_forms_sampled(eng, n):
+    pos = synth.nbody_bodies(n, seed=n)
+    which = ("plain", "direct", "persistent") + (("serve",) if n in (32767, 32768) else ())
+    at = sorted({0, 63, 64, n // 2, n - 65, n - 2, n - 1})
+    ref = {i: O.nbody_acc_body(pos, EPS2, i, True) for i in at}
+    for name, out in forms(eng, pos, 1, which):
+        assert not np.isnan(out).any(), (name, n)
+        for i in at:
+            assert same(out[i], ref[i]), (name, n, i)
