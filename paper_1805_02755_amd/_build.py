@@ -71,7 +71,7 @@ def _embed_headers() -> str:
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     objs = []
-    for src in ("kernels.hip", "batch_kernels.hip", "serve_kernels.hip", "noalloc.hip"):
+    for src in ("kernels.hip", "binomial_call.hip", "batch_kernels.hip", "serve_kernels.hip", "noalloc.hip"):
         o = os.path.join(BUILD, src + ".o")
         _run([HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, src), "-o", o], verbose)
         objs.append(o)

@@ -555,85 +555,198 @@ struct NbodyStepTile {
 };
 
 // Binomial option pricing: a granule is one work-group pricing four calls
-// (one float4 of spots). Thread j holds leaf j of all four trees. At each
-// level of the backward induction a node needs its upper neighbour, held by
-// the next lane: inside a wave it arrives by a DPP wave shift, and only the
-// first lane of each wave goes through LDS, to the last lane of the wave
-// below, after one barrier per level. Waves whose nodes all lie above the
-// level skip the arithmetic; inside a working wave every lane computes, and
-// lanes above the level produce values that no later level reads. The loop
-// is bound by barrier latency and issue, so the persistent kernel is asked
-// for eight resident workgroups per CU, as many as a plain launch reaches.
+// (one float4 of spots). At each level of the backward induction a node is
+// pu V[j+1] + pd V[j] (two products, then their sum), so a tree of N levels
+// takes 3 N (N + 1) / 2 instructions per call at the least. Two forms keep a
+// tree inside a wave, with no barrier, and differ in how many lanes share it.
+//
+// pu and pd are held in vector registers: a product with a scalar operand
+// issues at half the rate.
+__device__ __forceinline__ float binomial_constant(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ float binomial_leaf(float S, float f, float X) {
+  const float a = S * f - X;
+  return a > 0.0f ? a : 0.0f;
+}
+
+// Group form: a wave prices one group. Lane i holds leaves 4i .. 4i+3 of each
+// call, so only the last of four nodes needs another lane's value (a product
+// with a DPP wave shift, no instruction of its own), and lanes above the level
+// produce values that no later level reads. When the nodes left fit half the
+// lanes, two calls' registers are merged into one (the upper half of one
+// swapped with the lower half of the other), and again at a quarter, so that
+// at most half of the lanes idle; trees of fewer levels start merged. Bound by
+// VALU issue: 254 steps, 256 groups 56.6 -> 23.8 us, 4096 groups 137 -> 66 us,
+// against a workgroup per pair of groups with a barrier at every level.
 struct BinomialTile {
   static constexpr int kMinBlocksPerCu = 8;
-  static constexpr uint32_t kWaves = kBlockThreads / 64;
+  static constexpr uint32_t kGroupsPerTile = kBlockThreads / 64;
   ce_binomial_params p;
   const float4* spots;
   const float* factors;
   float4* out;
   __device__ void load_constants() {}
   __host__ __device__ uint64_t granules() const { return p.n_groups; }
-  // A tile is two consecutive groups (the last tile of a package may hold
-  // one): both trees advance together, so each barrier serves twice the work.
-  static constexpr uint32_t kGroupsPerTile = 2;
   __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
     return (uint32_t)((g1 - g0 + kGroupsPerTile - 1) / kGroupsPerTile);
   }
-  // Lane i receives lane i + 1's value (DPP wave_shl:1); the last lane,
-  // which has no source, keeps `top`.
-  static __device__ float from_next_lane(float x, float top) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(top), __float_as_int(x), 0x130, 0xf, 0xf, false));
+  // Lane i receives lane i + 1's value (DPP wave_shl:1), the last lane zero.
+  static __device__ __forceinline__ float from_next_lane(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kDppWaveShl1, 0xf, 0xf, true));
   }
-  __device__ float4 leaves(float4 S, float f, float X) const {
-    const float a = S.x * f - X, b = S.y * f - X, c = S.z * f - X, d = S.w * f - X;
-    return make_float4(a > 0.0f ? a : 0.0f, b > 0.0f ? b : 0.0f, c > 0.0f ? c : 0.0f, d > 0.0f ? d : 0.0f);
+  // One level of kSets calls (or sets of merged calls), four nodes per lane.
+  template <int kSets>
+  static __device__ __forceinline__ void level(float (&v)[kSets][4], float pu, float pd) {
+#pragma unroll
+    for (int s = 0; s < kSets; ++s) {
+      const float up = pu * from_next_lane(v[s][0]);
+      v[s][0] = pu * v[s][1] + pd * v[s][0];
+      v[s][1] = pu * v[s][2] + pd * v[s][1];
+      v[s][2] = pu * v[s][3] + pd * v[s][2];
+      v[s][3] = up + pd * v[s][3];
+    }
   }
-  __device__ void level(float4& v, const float4& top, float pu, float pd) const {
-    const float ux = from_next_lane(v.x, top.x), uy = from_next_lane(v.y, top.y);
-    const float uz = from_next_lane(v.z, top.z), uw = from_next_lane(v.w, top.w);
-    v.x = pu * ux + pd * v.x;
-    v.y = pu * uy + pd * v.y;
-    v.z = pu * uz + pd * v.z;
-    v.w = pu * uw + pd * v.w;
+  // a takes b's lower half into its upper half
+  static __device__ __forceinline__ float merge_halves(float a, float b) {
+    return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false)[0]);
+  }
+  // rows 1 and 3 of a take rows 0 and 2 of b
+  static __device__ __forceinline__ float merge_rows(float a, float b) {
+    return __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false)[0]);
   }
   __device__ void run(uint64_t g0, uint64_t g1, uint32_t t) const {
-    // edge[L & 1][k][w] holds the level-L value of the first lane of wave w
-    // for the tile's group k; slot kWaves is never written and feeds only
-    // the unused last leaf.
-    __shared__ float4 edge[2][kGroupsPerTile][kWaves + 1];
-    const uint64_t grp = g0 + (uint64_t)t * kGroupsPerTile;
-    const bool two = grp + 1 < g1;  // uniform across the workgroup
-    const uint32_t j = threadIdx.x;
-    const uint32_t w = __builtin_amdgcn_readfirstlane(j >> 6);
-    const uint32_t n = p.steps;
-    const float4 S0 = spots[grp];
-    const float4 S1 = two ? spots[grp + 1] : S0;
-    const float X = p.strike, pu = p.pu, pd = p.pd;
-    float4 v0 = make_float4(0.f, 0.f, 0.f, 0.f), v1 = v0;
-    if (j <= n) {
-      const float f = factors[j];
-      v0 = leaves(S0, f, X);
-      v1 = leaves(S1, f, X);
-    }
-    // Level L's copy of edge is rewritten at level L - 2, after the barrier of
-    // level L - 1 that follows every read of it, so one barrier per level suffices.
-    for (uint32_t L = n; L-- > 0;) {
-      float4(*e)[kWaves + 1] = edge[L & 1];
-      if ((j & 63) == 0) {
-        e[0][w] = v0;
-        e[1][w] = v1;
+    const uint32_t tid = thread_index();
+    const uint64_t grp = g0 + (uint64_t)t * kGroupsPerTile + __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (grp >= g1) return;
+    const uint32_t lane = tid & 63u, n = p.steps;
+    const float X = p.strike, pu = binomial_constant(p.pu), pd = binomial_constant(p.pd);
+    const float4 S = spots[grp];
+    const auto leaf = [&](float s, uint32_t j) { return j <= n ? binomial_leaf(s, factors[j], X) : 0.0f; };
+    uint32_t l = n;    // the level held: nodes 0 .. l
+    float half[2][4];  // calls x|y and z|w, 32 lanes each
+    if (n > 127) {
+      float v[4][4];
+#pragma unroll
+      for (uint32_t r = 0; r < 4; ++r) {
+        v[0][r] = leaf(S.x, lane * 4 + r);
+        v[1][r] = leaf(S.y, lane * 4 + r);
+        v[2][r] = leaf(S.z, lane * 4 + r);
+        v[3][r] = leaf(S.w, lane * 4 + r);
       }
-      __syncthreads();
-      if (w * 64 <= L) {
-        const float4 top0 = e[0][w + 1], top1 = e[1][w + 1];
-        level(v0, top0, pu, pd);
-        level(v1, top1, pu, pd);
+#pragma unroll 1
+      for (; l > 127; --l) level<4>(v, pu, pd);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        half[0][r] = merge_halves(v[0][r], v[1][r]);
+        half[1][r] = merge_halves(v[2][r], v[3][r]);
+      }
+    } else {
+      const float s0 = lane < 32 ? S.x : S.y, s1 = lane < 32 ? S.z : S.w;
+#pragma unroll
+      for (uint32_t r = 0; r < 4; ++r) {
+        half[0][r] = leaf(s0, (lane & 31u) * 4 + r);
+        half[1][r] = leaf(s1, (lane & 31u) * 4 + r);
       }
     }
-    if (j == 0) {
-      out[grp] = v0;
-      if (two) out[grp + 1] = v1;
+#pragma unroll 1
+    for (; l > 63; --l) level<2>(half, pu, pd);
+    float row[1][4];  // calls x, z, y, w, 16 lanes each
+#pragma unroll
+    for (int r = 0; r < 4; ++r) row[0][r] = merge_rows(half[0][r], half[1][r]);
+#pragma unroll 1
+    for (; l > 0; --l) level<1>(row, pu, pd);
+    if ((lane & 15u) == 0) {
+      const uint32_t q = lane >> 4;
+      reinterpret_cast<float*>(out + grp)[(q & 1u) * 2 + (q >> 1)] = row[0][0];
     }
+  }
+};
+
+// Call form, where the groups fill the GPU: a lane prices one call, its nodes
+// in registers, so nothing moves between lanes and no lane idles. A level is
+// unrolled over the nodes still alive, to the next multiple of 16. 256
+// registers hold nodes 0 .. 191; a deeper tree first runs its nodes from 192
+// up through all their levels and leaves node 192's value of each level in
+// LDS (64 KiB per workgroup), where the lower nodes take it up. Two workgroups
+// per compute unit: two waves per SIMD, which issue at 2.1 cycles per
+// instruction of a possible 2. 254 steps: 1,048,576 groups 27.3 -> 5.95 ms
+// (12.0 in the group form), 32,768 groups 887 -> 206 us (410), 16,384 groups
+// about 190 (205), 8,192 188 (120): a wave takes 185 us however few there are.
+struct BinomialCallTile {
+  static constexpr int kMinBlocksPerCu = 2;
+  static constexpr uint32_t kGroupsPerTile = kBlockThreads / 4;
+  static constexpr int kLow = 192, kHigh = 64, kStep = 16;
+  ce_binomial_params p;
+  const float4* spots;
+  const float* factors;
+  float4* out;
+  __device__ void load_constants() {}
+  __host__ __device__ uint64_t granules() const { return p.n_groups; }
+  __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
+    return (uint32_t)((g1 - g0 + kGroupsPerTile - 1) / kGroupsPerTile);
+  }
+  // One level of nodes 0 .. kCount - 2 (the node above each is in v).
+  template <int kCount, int kSize>
+  static __device__ __forceinline__ void level(float (&v)[kSize], float pu, float pd) {
+#pragma unroll
+    for (int k = 0; k + 1 < kCount; ++k) v[k] = pu * v[k + 1] + pd * v[k];
+  }
+  // From level l down to 0 of the nodes 0 .. kCount - 1, fewer at each level.
+  template <int kCount>
+  static __device__ __forceinline__ void low_levels(float (&v)[kLow], uint32_t& l, float pu, float pd) {
+    if constexpr (kCount > 0) {
+#pragma unroll 1
+      for (; l + kStep >= kCount && l > 0; --l) level<kCount>(v, pu, pd);
+      low_levels<kCount - kStep>(v, l, pu, pd);
+    }
+  }
+  // From level l down to kLow of the nodes kLow .. kLow + kCount - 1, node
+  // kLow's value of each level into `edge`.
+  template <int kCount>
+  static __device__ __forceinline__ void high_levels(float (&u)[kHigh], uint32_t& l, float (*edge)[64], uint32_t lane,
+                                                     float pu, float pd) {
+    if constexpr (kCount > 0) {
+#pragma unroll 1
+      for (; l - kLow + kStep >= kCount && l > kLow; --l) {
+        level<kCount>(u, pu, pd);
+        edge[l - 1 - kLow][lane] = u[0];
+      }
+      high_levels<kCount - kStep>(u, l, edge, lane, pu, pd);
+    }
+  }
+  __device__ void run(uint64_t g0, uint64_t g1, uint32_t t) const {
+    __shared__ float fac[kLow + kHigh];
+    __shared__ float edges[kBlockThreads / 64][kHigh][64];  // a wave's own: [level - kLow][lane]
+    const uint32_t tid = thread_index(), lane = tid & 63u, n = p.steps;
+    const uint64_t call = (g0 + (uint64_t)t * kGroupsPerTile) * 4 + tid, end = g1 * 4;
+    __syncthreads();  // the tile before is done with `fac`
+    fac[tid] = factors[tid <= n ? tid : n];
+    __syncthreads();
+    const float S = reinterpret_cast<const float*>(spots)[call < end ? call : end - 1];
+    const float X = p.strike, pu = binomial_constant(p.pu), pd = binomial_constant(p.pd);
+    float(*const edge)[64] = edges[tid >> 6];
+    if (n >= kLow) {
+      float u[kHigh];
+#pragma unroll
+      for (int k = 0; k < kHigh; ++k) u[k] = binomial_leaf(S, fac[kLow + k], X);
+      uint32_t l = n;
+      edge[l - kLow][lane] = u[0];
+      high_levels<kHigh>(u, l, edge, lane, pu, pd);
+    }
+    float v[kLow];
+#pragma unroll
+    for (int k = 0; k < kLow; ++k) v[k] = binomial_leaf(S, fac[k], X);
+    uint32_t l = n;
+#pragma unroll 1
+    for (; l >= kLow; --l) {
+      const float top = edge[l - kLow][lane];
+      level<kLow>(v, pu, pd);
+      v[kLow - 1] = pu * top + pd * v[kLow - 1];
+    }
+    low_levels<kLow>(v, l, pu, pd);
+    if (call < end) reinterpret_cast<float*>(out)[call] = v[0];
   }
 };
 

@@ -222,7 +222,7 @@ struct ce_engine {
   ce_nbody_step_params nbs{};
   ce_binomial_params bin{};
   static constexpr int kOccSlots = 16;
-  int occ_cache[kOccSlots] = {};  // persistent workgroups per CU by (kernel id, strict)
+  int occ_cache[kOccSlots] = {};  // persistent workgroups per CU by (kernel id, form)
   Binding in[kMaxSlots];
   Binding out[kMaxSlots];
   uint32_t pat_outs = 1, pat_items = 1;
@@ -359,6 +359,21 @@ struct ce_engine {
   // reads every position once per body block; a runtime payload may read
   // its inputs any number of times.
   bool reads_input_once() const { return kernel_id == CE_KERNEL_BLUR5 || kernel_id == CE_KERNEL_BINOMIAL; }
+  // The binomial form of this run, from the GPU's share of the groups and the
+  // smallest package the scheduler may hand it.
+  bool binomial_by_call() const {
+    const uint64_t G = bin.n_groups;
+    uint64_t share = G, package = G;
+    if (sched.kind == CE_SCHED_STATIC) {
+      if (use_host()) share = (uint64_t)((double)G * std::min(1.0, std::max(0.0, sched.props[0])));
+      package = sched.n_packages ? G / sched.n_packages : share;
+    } else if (sched.kind == CE_SCHED_DYNAMIC) {
+      package = sched.package_granules ? sched.package_granules : ceil_div(G, std::max<uint32_t>(1, sched.n_packages));
+    } else if (sched.min_granules[0]) {
+      package = sched.min_granules[0];
+    }
+    return binomial_call_form(share, package);
+  }
   uint64_t items_in(uint64_t g0, uint64_t g1) const {
     switch (kernel_id) {
       case CE_KERNEL_ESCAPE: return (g1 - g0) * esc.w;
@@ -996,6 +1011,7 @@ struct ce_engine {
     kargs.nb = nb;
     kargs.nbs = nbs;
     kargs.bin = bin;
+    kargs.bin_call = kernel_id == CE_KERNEL_BINOMIAL && use_gpu() && binomial_by_call();
     const void* gin[kMaxSlots] = {nullptr, nullptr};
     if (use_gpu()) {
       for (int s = 0; s < n_in_slots(); ++s) {
@@ -1096,7 +1112,7 @@ struct ce_engine {
     uint32_t grid = 0, gather_wgs = 0, resident_wgs = 0;
     if (use_gpu()) {
       // resident workgroups per CU: a property of the compiled kernel, asked once per payload
-      const int occ_key = kernel_id * 2 + (kargs.strict ? 1 : 0);
+      const int occ_key = kernel_id * 2 + ((kernel_id == CE_KERNEL_BINOMIAL ? kargs.bin_call : kargs.strict) ? 1 : 0);
       int bpc = occ_key < kOccSlots ? occ_cache[occ_key] : 0;
       if (bpc == 0) {
         if ((he = persistent_blocks_per_cu(kargs, &bpc)) != hipSuccess) return hip_fail(he, "run: occupancy");
@@ -2097,6 +2113,7 @@ ce_status ce_bare_run_outs(int kernel_id, const void* params, size_t params_size
       if (params_size != sizeof(ce_binomial_params) || !ins || !ins[0] || !ins[1]) return CE_E_INVALID;
       memcpy(&a.bin, params, sizeof a.bin);
       if (a.bin.n_groups == 0 || a.bin.steps == 0 || a.bin.steps + 1 > kBlockThreads) return CE_E_INVALID;
+      a.bin_call = binomial_call_form(a.bin.n_groups, a.bin.n_groups);
       a.in0 = ins[0];
       a.in1 = ins[1];
       break;

@@ -124,7 +124,7 @@ uint32_t gpu_tiles(const KernelArgs& a, uint64_t g0, uint64_t g1) {
       return a.strict ? make_nbody<true>(a).ntiles(g0, g1) : make_nbody<false>(a).ntiles(g0, g1);
     case CE_KERNEL_NBODY_STEP:
       return a.strict ? make_nbody_step<true>(a).ntiles(g0, g1) : make_nbody_step<false>(a).ntiles(g0, g1);
-    case CE_KERNEL_BINOMIAL: return make_binomial(a).ntiles(g0, g1);
+    case CE_KERNEL_BINOMIAL: return a.bin_call ? binomial_call_tiles(a, g0, g1) : make_binomial(a).ntiles(g0, g1);
     case CE_KERNEL_RUNTIME: return make_rt(a).ntiles(g0, g1);
   }
   return 0;
@@ -147,6 +147,7 @@ hipError_t persistent_blocks_per_cu(const KernelArgs& a, int* blocks) {
                       : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_persistent<NbodyStepTile<false>>,
                                                                      kBlockThreads, 0);
     case CE_KERNEL_BINOMIAL:
+      if (a.bin_call) return binomial_call_blocks_per_cu(blocks);
       return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_persistent<BinomialTile>, kBlockThreads, 0);
     case CE_KERNEL_RUNTIME:
       if (!a.rt_fn_persistent) return hipErrorInvalidValue;
@@ -173,7 +174,12 @@ hipError_t launch_persistent(const KernelArgs& a, const SchedArgs& s, uint32_t g
       else
         hipLaunchKernelGGL(k_persistent<NbodyStepTile<false>>, g, b, 0, st, make_nbody_step<false>(a), s);
       break;
-    case CE_KERNEL_BINOMIAL: hipLaunchKernelGGL(k_persistent<BinomialTile>, g, b, 0, st, make_binomial(a), s); break;
+    case CE_KERNEL_BINOMIAL:
+      if (a.bin_call)
+        launch_binomial_call_persistent(a, s, grid, st);
+      else
+        hipLaunchKernelGGL(k_persistent<BinomialTile>, g, b, 0, st, make_binomial(a), s);
+      break;
     case CE_KERNEL_RUNTIME: {
       if (!a.rt_fn_persistent) return hipErrorInvalidValue;
       RtTile pay = make_rt(a);
@@ -204,7 +210,10 @@ hipError_t launch_direct(const KernelArgs& a, const DirectArgs& d, uint32_t grid
       else
         launch_nbody_direct(make_nbody_step<false>(a), d, grid, st);
       break;
-    case CE_KERNEL_BINOMIAL: hipLaunchKernelGGL(k_direct<BinomialTile>, g, b, 0, st, make_binomial(a), d); break;
+    case CE_KERNEL_BINOMIAL:
+      if (a.bin_call) return hipErrorInvalidValue;  // dealt by tickets
+      hipLaunchKernelGGL(k_direct<BinomialTile>, g, b, 0, st, make_binomial(a), d);
+      break;
     case CE_KERNEL_RUNTIME: {
       if (!a.rt_fn_direct) return hipErrorInvalidValue;
       RtTile pay = make_rt(a);
@@ -238,7 +247,12 @@ hipError_t launch_bare(const KernelArgs& a, hipStream_t st) {
       else
         launch_nbody_bare(make_nbody_step<false>(a), G, tiles, st);
       break;
-    case CE_KERNEL_BINOMIAL: hipLaunchKernelGGL(k_bare<BinomialTile>, g, b, 0, st, make_binomial(a), G); break;
+    case CE_KERNEL_BINOMIAL:
+      if (a.bin_call)
+        launch_binomial_call_bare(a, G, tiles, st);
+      else
+        hipLaunchKernelGGL(k_bare<BinomialTile>, g, b, 0, st, make_binomial(a), G);
+      break;
     case CE_KERNEL_RUNTIME: {
       if (!a.rt_fn_bare) return hipErrorInvalidValue;
       RtTile pay = make_rt(a);

@@ -20,6 +20,7 @@ struct KernelArgs {
   ce_nbody_params nb;
   ce_nbody_step_params nbs;
   ce_binomial_params bin;
+  uint32_t bin_call;        // binomial: one lane per call (binomial_call_form) rather than a wave per group
   const void* in0;          // device pointers
   const void* in1;
   void* out;
@@ -44,6 +45,11 @@ hipError_t persistent_blocks_per_cu(const KernelArgs& a, int* blocks);
 hipError_t launch_persistent(const KernelArgs& a, const SchedArgs& s, uint32_t grid, hipStream_t st);
 hipError_t launch_direct(const KernelArgs& a, const DirectArgs& d, uint32_t grid, hipStream_t st);
 hipError_t launch_bare(const KernelArgs& a, hipStream_t st);
+// The binomial payload's call form (binomial_call.hip), for the functions above.
+uint32_t binomial_call_tiles(const KernelArgs& a, uint64_t g0, uint64_t g1);
+hipError_t binomial_call_blocks_per_cu(int* blocks);
+void launch_binomial_call_persistent(const KernelArgs& a, const SchedArgs& s, uint32_t grid, hipStream_t st);
+void launch_binomial_call_bare(const KernelArgs& a, uint64_t G, uint32_t tiles, hipStream_t st);
 // Runtime payloads (rt_module.cpp): compile the caller's work-item source
 // for gfx950 (no GPU needed), and compile and load it on the current device.
 // 0 on success; otherwise negative with the compiler's log.
