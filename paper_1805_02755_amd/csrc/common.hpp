@@ -18,6 +18,7 @@ enum SchedKind : uint32_t { kStatic = 0, kDynamic = 1, kHGuided = 2 };
 // 2-D payloads: a tile is kTileRows rows by one column block.
 constexpr uint32_t kEscapeTileRows = 1;
 constexpr uint32_t kEscapeTileCols = 512;
+constexpr uint32_t kEscapeBlockCols = 16, kEscapeBlockRows = 4;  // pixels of one wave
 constexpr uint32_t kBlurTileRows = 32;
 constexpr uint32_t kBlurTileCols = 1024;  // 256 threads x 4 columns
 constexpr uint32_t kNbodyGranule = 256;   // bodies per granule (1-D lws)

@@ -12,7 +12,7 @@ namespace ce {
 // first n >= 1 with |z_n|^2 > 4, capped at max_iter; one step is x2 = zr zr,
 // y2 = zi zi, zi <- fma(zr + zr, zi, ci), zr <- (x2 - y2) + cr.
 //
-// The main loop takes kBlock steps per test and keeps a = 2 zr, b = 2 zi,
+// The main loop takes 8 or 16 steps per test and keeps a = 2 zr, b = 2 zi,
 // whose step b <- fma(a, b, 2 ci), a <- fma(a a - b b, 1/2, 2 cr) is five
 // instructions with the same roundings (every operation is the plain step's,
 // scaled by a power of two). Three facts make its counts those of the plain
@@ -20,8 +20,8 @@ namespace ce {
 //  - |c|^2 <= 3.9999: once |z|^2 > 4 in FP32, |z'| >= |z|^2 - |c| keeps it
 //    above 4 by 5e-5 or more, far beyond the rounding, at every later step
 //    (to infinity and NaN, which fail the test too). So one test per block
-//    sees every escape, and the steps of that block are taken again one by
-//    one to find where.
+//    sees every escape, and counting the steps of that block that are still
+//    inside finds where.
 //  - a component of c of at least 2^-20, and ci zero or at least 2^-60: a
 //    product that underflows (rounded differently when scaled) is then added
 //    to something it is far too small to change, or is the whole of a zr
@@ -34,45 +34,48 @@ namespace ce {
 //    a cycle within some tens to hundreds of steps, where the plain loop runs
 //    to max_iter: they are nearly all the work of an image with a high cap.
 // Every other c takes the plain loop from the start (|c| > 2 escapes at
-// once, c = -2 is a cycle), except that a c below 2^-20 in both components stays below 2^-19.
+// once, c = -2 is a cycle), except that a c below 2^-20 in both components
+// stays below 2^-19.
 //
-// Bound by FP32 issue, and by the longest orbit of a wave where the image is
-// small. A run of the whole set, against four plain steps per test: 8192 x
-// 8192 with max_iter 4096 9.75 -> 1.64 ms; 256 x 256 with 256 24.4 -> 19.7 us
-// (kernel 13.9 -> 9.1); the batch of 256 jobs 20.2 -> 4.1 ms.
-// max_iter must be the same in every lane of the wave; which lanes are still
-// in the main loop is kept as one wave-uniform mask, and a lane that has left
-// computes on without effect, so that the loop holds no per-lane branch.
-__device__ __forceinline__ void escape_step(float& a, float& b, float cr2, float ci2) {
-  const float d = a * a - b * b;
-  b = __builtin_fmaf(a, b, ci2);
-  a = __builtin_fmaf(d, 0.5f, cr2);
-}
-
-__device__ __forceinline__ uint32_t escape_count(float cr, float ci, uint32_t max_iter) {
-  constexpr uint32_t kBlock = 8;
-  const float big = 0x1p-20f, least = 0x1p-60f;
-  const float mr = __builtin_fabsf(cr), mi = __builtin_fabsf(ci);
-  const uint32_t cap = __builtin_amdgcn_readfirstlane(max_iter);
-  const uint32_t lane = __lane_id();
-  const float cr2 = cr + cr, ci2 = ci + ci;
-  float a = 0.0f, b = 0.0f;    // the state after m steps
-  float ea = 0.0f, eb = 0.0f;  // the state after n steps of a lane that has left
-  uint32_t m = 0, n = 0;
-  const bool tiny = mr < big && mi < big;
-  if (tiny) n = cap;
-  uint64_t live = __builtin_amdgcn_ballot_w64(!tiny && cr * cr + ci * ci <= 3.9999f && (ci == 0.0f || mi >= least));
-  uint64_t escaped = 0, cycled = 0;
-  for (uint32_t run = kBlock; live != 0 && m + kBlock <= cap; run *= 2) {
+// The first block counts as it goes (most points outside escape in it); later
+// blocks only test, and the block an orbit escaped in is taken again. Blocks
+// of 16 from step 64 on halve what a block costs besides its steps.
+//
+// Bound by FP32 issue, and by the longest orbit where the image is small. A
+// run on the GPU alone, against four plain steps per test (and rows of 512
+// pixels dealt by tickets): the whole set at 8192 x 8192 with max_iter 4096
+// 9.0 -> 0.90 ms, 1920 x 1080 with 1000 368 -> 51 us, 1024 x 1024 with 256
+// 40 -> 26 us, 256 x 256 24 -> 18 us (of which 15 are the launch and the
+// wait for it); the batch of 256 jobs 19.1 -> 4.1 ms. max_iter must be the same in every lane of the wave; which lanes are
+// still in the main loop is kept as one wave-uniform mask, and a lane that has
+// left computes on without effect, so that the loop holds no per-lane branch.
+struct EscapeOrbit {
+  float cr2, ci2;              // 2 c
+  float a = 0.0f, b = 0.0f;    // 2 z after m steps
+  float ea = 0.0f, eb = 0.0f;  // 2 z after n steps, of a lane that has left
+  uint32_t lane, m = 0, n = 0;
+  uint64_t live = 0;           // lanes in the main loop
+  uint64_t escaped = 0;        // lanes that left it in the block from step n on
+  uint64_t cycled = 0;         // lanes that left it in a cycle
+  __device__ __forceinline__ void step(float& x, float& y) const {
+    const float d = x * x - y * y;
+    y = __builtin_fmaf(x, y, ci2);
+    x = __builtin_fmaf(d, 0.5f, cr2);
+  }
+  static __device__ __forceinline__ bool inside(float x, float y) { return x * x + y * y <= 16.0f; }
+  __device__ __forceinline__ bool has(uint64_t mask) const { return ((mask >> lane) & 1u) != 0; }
+  // Blocks of kBlock steps while a lane is left and the next block ends by `stop`.
+  template <uint32_t kBlock>
+  __device__ __forceinline__ void blocks(uint32_t stop) {
+    if (live == 0 || m + kBlock > stop) return;
     const uint32_t ka = __float_as_uint(a), kb = __float_as_uint(b);  // the state kept
-    const uint32_t stop = cap - m > run ? m + run : cap;
     do {
       float u = a, v = b;
 #pragma unroll
-      for (uint32_t k = 0; k < kBlock; ++k) escape_step(u, v, cr2, ci2);
-      const uint64_t out = live & ~__builtin_amdgcn_ballot_w64(u * u + v * v <= 16.0f);
+      for (uint32_t k = 0; k < kBlock; ++k) step(u, v);
+      const uint64_t out = live & ~__builtin_amdgcn_ballot_w64(inside(u, v));
       if (out != 0) {
-        if ((out >> lane) & 1u) {
+        if (has(out)) {
           ea = a;
           eb = b;
           n = m;
@@ -89,27 +92,76 @@ __device__ __forceinline__ uint32_t escape_count(float cr, float ci, uint32_t ma
       live &= ~back;
     } while (live != 0 && m + kBlock <= stop);
   }
-  if (escaped != 0) {
-    // where in its block a lane escaped: |z|^2 stays above 4 from there on
-    float u = ea, v = eb;
-    uint32_t q = n + 1;
+};
+
+__device__ __forceinline__ uint32_t escape_count(float cr, float ci, uint32_t max_iter) {
+  constexpr uint32_t kFirst = 8, kLong = 64;
+  const float big = 0x1p-20f, least = 0x1p-60f;
+  const float mr = __builtin_fabsf(cr), mi = __builtin_fabsf(ci);
+  const uint32_t cap = __builtin_amdgcn_readfirstlane(max_iter);
+  EscapeOrbit o;
+  o.lane = __lane_id();
+  o.cr2 = cr + cr;
+  o.ci2 = ci + ci;
+  const bool tiny = mr < big && mi < big;
+  uint32_t q = tiny ? cap : 0u;  // the count, of a lane that has one
+  bool counted = tiny;
+  const bool fast = !tiny && cr * cr + ci * ci <= 3.9999f && (ci == 0.0f || mi >= least);
+  if (kFirst <= cap) {
+    float u = 0.0f, v = 0.0f;
+    uint32_t in = 1;
+    bool last = false;
 #pragma unroll
-    for (uint32_t k = 1; k < kBlock; ++k) {
-      escape_step(u, v, cr2, ci2);
-      q += u * u + v * v <= 16.0f ? 1u : 0u;
+    for (uint32_t k = 1; k <= kFirst; ++k) {
+      o.step(u, v);
+      last = EscapeOrbit::inside(u, v);
+      if (k < kFirst) in += last ? 1u : 0u;
     }
-    if ((escaped >> lane) & 1u) return q;
+    if (fast && !last) {
+      q = in;
+      counted = true;
+    }
+    o.live = __builtin_amdgcn_ballot_w64(fast && last);
+    o.a = u;
+    o.b = v;
+    o.m = kFirst;
+    // to steps 16, 32, 64 in blocks of 8, then to each power of two in blocks
+    // of 16, the state at each start kept for the cycle test
+    uint32_t next = 2 * kFirst;
+    for (; o.live != 0 && o.m + kFirst <= cap && next <= kLong; next *= 2) o.blocks<8>(next < cap ? next : cap);
+    for (; o.live != 0 && o.m + 16 <= cap; next *= 2) o.blocks<16>(next < cap ? next : cap);
+    o.blocks<8>(cap);
+    if (o.escaped != 0) {
+      float x = o.ea, y = o.eb;
+      uint32_t e = o.n + 1;
+#pragma unroll
+      for (uint32_t k = 1; k < 8; ++k) {
+        o.step(x, y);
+        e += EscapeOrbit::inside(x, y) ? 1u : 0u;
+      }
+      if (o.m > kLong) {  // some block may have been one of 16
+#pragma unroll
+        for (uint32_t k = 8; k < 16; ++k) {
+          o.step(x, y);
+          e += EscapeOrbit::inside(x, y) ? 1u : 0u;
+        }
+      }
+      if (o.has(o.escaped)) {
+        q = e;
+        counted = true;
+      }
+    }
+    if (o.has(o.cycled)) {
+      q = cap;
+      counted = true;
+    }
   }
-  if ((cycled >> lane) & 1u) n = cap;
-  if ((live >> lane) & 1u) {
-    ea = a;
-    eb = b;
-    n = m;
-  }
+  if (counted) return q;
   // The plain loop: the last steps before the cap, and every step of the c
   // that the main loop does not take. It looks for cycles too: c = -2, a
   // corner of many images, stays on z = 2.
-  float zr = 0.5f * ea, zi = 0.5f * eb, kr = zr, ki = zi;
+  uint32_t n = o.has(o.live) ? o.m : 0u;
+  float zr = n != 0 ? 0.5f * o.a : 0.0f, zi = n != 0 ? 0.5f * o.b : 0.0f, kr = zr, ki = zi;
   while (n < cap) {
     const float x2 = zr * zr;
     const float y2 = zi * zi;

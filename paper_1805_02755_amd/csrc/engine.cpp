@@ -1283,19 +1283,24 @@ struct ce_engine {
       // runs (the overhead of a single-device run is then that of a plain
       // launch).
       light_exit = !gather && grid <= kFastExitMaxWgs;
-      // Tiles of very different cost over more than four rounds, all of
+      // Runtime tiles, of unknown cost, over more than four rounds, all of
       // them this device's: one workgroup per tile, dealt by the hardware as
       // slots free up (each slot is refilled as soon as its workgroup ends,
       // where a persistent workgroup's waves wait at every tile's barrier
-      // for the slowest of them), swizzled over the XCDs. Escape-time on the
-      // GPU alone, against atomic tickets: 2048^2 (4 rounds) 0.105 against
-      // 0.097 ms, 2560^2 0.099 against 0.140, 3072^2 0.125 against 0.177,
-      // 3584^2 0.168 against 0.220, 4096^2 0.241 against 0.246.
+      // for the slowest of them), swizzled over the XCDs. Measured on
+      // escape-time rows of 512 pixels against atomic tickets: 2048^2 (4
+      // rounds) 0.105 against 0.097 ms, 2560^2 0.099 against 0.140, 3072^2
+      // 0.125 against 0.177, 4096^2 0.241 against 0.246.
       const bool uneven_one_shot = light_exit && gs.pre_only && !gs.stride && !grid_override &&
-                                   (kernel_id == CE_KERNEL_ESCAPE || kernel_id == CE_KERNEL_RUNTIME) &&
+                                   kernel_id == CE_KERNEL_RUNTIME &&
                                    gs.pre_nt > kDirectOneShotRounds * (uint64_t)resident_wgs &&
                                    gs.pre_nt <= kFastExitMaxWgs;
-      fast_exit = light_exit && gs.pre_only && (gs.stride || uneven_one_shot);
+      // Escape-time on the GPU alone has no tiles to deal: its direct kernel
+      // sweeps the package (launch_direct), folding the workgroups planned
+      // here, one per tile, into as many as it runs fastest with.
+      const bool sweep = light_exit && gs.pre_only && kernel_id == CE_KERNEL_ESCAPE;
+      if (sweep && !grid_override) grid = std::min<uint32_t>(gs.pre_nt, kFastExitMaxWgs);
+      fast_exit = light_exit && gs.pre_only && (gs.stride || uneven_one_shot || sweep);
       // The fast path never touches its queue state, which therefore stays
       // clear for the next run: the buffers keep their roles, and nothing is
       // cleared either.
@@ -1324,7 +1329,7 @@ struct ce_engine {
         // plain launch is. A fixed split over fewer workgroups keeps fewer
         // of them per CU than the hardware would (blur 16384^2: 1024
         // workgroups of eight tiles ran 2.8 % longer than 8192 of one).
-        if (!grid_override && gs.pre_nt >= kDirectOneShotRounds * (uint64_t)resident_wgs &&
+        if (!grid_override && !sweep && gs.pre_nt >= kDirectOneShotRounds * (uint64_t)resident_wgs &&
             gs.pre_nt <= kFastExitMaxWgs)
           grid = gs.pre_nt;
         if (uneven_one_shot) {

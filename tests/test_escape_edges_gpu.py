@@ -41,3 +41,32 @@ def test_counts_equal_the_oracles(region, max_iter):
     ce.ce_bare_run(ce.CE_KERNEL_ESCAPE, ce.ce_escape_params(w, h, x0, y0, dx, dy, max_iter), [], out)
     ref = O.escape(w, h, x0, y0, dx, dy, max_iter)
     assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
+
+
+@pytest.mark.parametrize("w,h", [(1, 1), (1, 700), (15, 3), (16, 4), (17, 5), (131, 96), (513, 33), (1025, 301),
+                                 (4100, 67)])
+def test_every_pixel_once_however_the_blocks_are_dealt(w, h):
+    """The direct sweep (GPU alone; also with one workgroup and with more than
+    it has blocks), tiles dealt by tickets and in packages, and the plain
+    launch write every pixel of a ragged grid."""
+    x0, y0, dx, dy = (float(np.float32(v)) for v in (-2.0, -1.5, 3.0 / w, 3.0 / h))
+    prm = ce.ce_escape_params(w, h, x0, y0, dx, dy, 300)
+    ref = O.escape(w, h, x0, y0, dx, dy, 300)
+    out = torch.full((h, w), -1, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    ce.ce_bare_run(ce.CE_KERNEL_ESCAPE, prm, [], out)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
+    with ce.Engine() as eng:
+        eng.use(ce.CE_DEV_GPU, 0, 0)
+        for workgroups in (0, 1, 7, 5000):
+            for sched in (dict(kind=ce.CE_SCHED_STATIC), dict(kind=ce.CE_SCHED_DYNAMIC, package_granules=7),
+                          dict(kind=ce.CE_SCHED_HGUIDED, power=[1], k=2, min_granules=[1])):
+                out.fill_(-1)
+                torch.cuda.synchronize()
+                eng.gpu_workgroups(workgroups)
+                eng.work_items([w, h])
+                eng.scheduler(**sched)
+                eng.program_kernel(ce.CE_KERNEL_ESCAPE, prm)
+                eng.program_out(0, dev=out, nbytes=w * h * 4)
+                eng.run()
+                assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), (workgroups, sched)
