@@ -1198,22 +1198,25 @@ struct ce_engine {
       }
       // Several tickets per atomic once there are several tiles per
       // workgroup: every ticket atomic goes to one counter, which serialises
-      // them (escape-time 3072^2, nine tiles per workgroup, one ticket each:
-      // twice the plain launch's time), while a large grab leaves the
+      // them (rows of an escape-time image, nine tiles per workgroup, one
+      // ticket each: twice the plain launch's time), while a large grab leaves the
       // workgroups uneven at the end. With k tiles per workgroup, taking
       // about sqrt(k) per atomic balances the two: sqrt(k) atomics per
       // workgroup and a last grab of sqrt(k) tiles (measured 2048^2 to
       // 8192^2: best at 2, 2-3, 4 and 8 for k = 4, 9, 16 and 64).
       const uint64_t per_wg = gpu_tiles(kargs, 0, G) / std::max<uint32_t>(1, grid - gather_wgs);
       gs.chunk = (uint32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, (uint64_t)std::lround(std::sqrt((double)per_wg))));
-      // Blur and n-body tiles all cost the same: a fixed round-robin needs no
-      // atomics. Escape-time tiles vary, but a tile is one row segment and a
-      // workgroup's rows lie far apart, which evens out its share; measured
-      // on the 1024 x 1024 grid the round-robin beat an atomic ticket per
-      // tile (52 us against 58 us), whose last round is one atomic per
-      // workgroup on a single counter. With gatherers sharing some CUs the
-      // fixed round-robin would leave the workgroups on those CUs behind, so
-      // tiles are dealt dynamically then.
+      // Blur and n-body tiles all cost the same, and escape-time tiles, whose
+      // blocks of pixels lie all over their package, nearly: a fixed
+      // round-robin needs no atomics, and a workgroup runs its tiles of a
+      // package one after another, its waves not waiting for each other in
+      // between (next_tile). Escape-time co-executed under HGuided, against
+      // atomic tickets: 2048^2 with max_iter 256 62 against 92 us, 1920 x
+      // 1080 with 1000 171 against 205, 3000^2 with 2000 0.62 against
+      // 0.84 ms, 4096^2 with 256 206 against 185 and, with the host slower,
+      // 172 against 183. With gatherers sharing some CUs the fixed
+      // round-robin would leave the workgroups on those CUs behind, so tiles
+      // are dealt dynamically then.
       // A binomial tile runs for tens of microseconds, so one atomic per tile
       // costs nothing, and dealing them one at a time keeps the GPU balanced
       // even when part of the grid becomes resident only as the rest leaves:
@@ -1221,15 +1224,11 @@ struct ce_engine {
       // share of tickets and run them on an otherwise idle GPU.
       const bool long_tiles = kernel_id == CE_KERNEL_BINOMIAL;
       if (long_tiles) gs.chunk = 1;
-      // Escape-time tiles of one column block over many rounds differ by
-      // orders of magnitude (8192^2: workgroup w would run every 128th row of
-      // one 512-pixel column, 64 tiles, the busiest columns all on the same
-      // workgroups), and a payload supplied at run time has tiles of unknown
-      // cost: beyond one round both are dealt by atomic tickets. Within one
-      // round every workgroup runs one tile either way, and the round-robin
-      // needs no atomic.
-      const bool uneven = (kernel_id == CE_KERNEL_ESCAPE || kernel_id == CE_KERNEL_RUNTIME) &&
-                          gpu_tiles(kargs, 0, G) > (uint64_t)(grid - gather_wgs);
+      // A payload supplied at run time has tiles of unknown cost: beyond one
+      // round they are dealt by atomic tickets. Within one round every
+      // workgroup runs one tile either way, and the round-robin needs no
+      // atomic.
+      const bool uneven = kernel_id == CE_KERNEL_RUNTIME && gpu_tiles(kargs, 0, G) > (uint64_t)(grid - gather_wgs);
       gs.stride = (gather || long_tiles || uneven) ? 0u : 1u;
       // the gatherers wait for the host's packages, whose length depends on the problem
       gs.gather_wait_ticks = std::max<uint64_t>(1, (uint64_t)((double)wallclock_hz * gather_wait_s));

@@ -161,6 +161,9 @@ __device__ void publish_dynamic(const T& pay, const SchedArgs& s, uint64_t tot, 
   if (end < g1) sys_store(&s.l1->gpu_flags, 1);
 }
 
+// Tiles a workgroup runs between two looks at the dispenser at most.
+constexpr uint32_t kTilesTogether = 16;
+
 // What one workgroup knows of the ticket chain, held by the lane that talks
 // to the dispenser: tickets taken but not yet run, the published total it
 // last read (it only grows, so it is a safe lower bound), the package of its
@@ -172,11 +175,11 @@ struct Cursor {  // zero-initialised at the start of a run
   uint64_t t_next, t_end;
   uint64_t tot_seen;
   uint64_t base, g0, g1;
-  uint64_t cur_t;  // ticket of the tile being run
+  uint64_t cur_t;  // last ticket of the tiles being run
   uint32_t p, nt;  // nt == 0: no package yet
 };
 
-// After a tile: if it held its package's last ticket, stamp the package end.
+// After tiles: if they held their package's last ticket, stamp the package end.
 __device__ __forceinline__ void tile_finished(const SchedArgs& s, const Cursor& c) {
   if (c.nt == 0 || c.cur_t + 1 != c.base + c.nt) return;
   dev_store(&s.pkgs[c.p].t_end, now_tick());
@@ -191,12 +194,17 @@ __device__ __forceinline__ void tile_finished(const SchedArgs& s, const Cursor& 
 // level-1 package, so the PCIe round trip of the claim overlaps the last
 // round of tiles. The GPU thus acts as one device towards the scheduler while
 // its workgroups share each package. Returns false when this workgroup
-// should leave.
+// should leave; otherwise it has *count_out tiles to run, *step_out apart:
+// besides the ticket's own, those of its next tickets that lie in the same
+// package and before the point where a ticket may have to claim. Waves of a
+// payload without barriers of its own run them one after another without
+// waiting for each other.
 template <class T>
-__device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t* ti_out) {
+__device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t* ti_out, uint32_t* count_out,
+                          uint32_t* step_out) {
   L2State* q = s.l2;
+  const uint64_t n = gridDim.x - s.gather_wgs;
   if (c.t_next == c.t_end) {
-    const uint64_t n = gridDim.x - s.gather_wgs;
     if (s.stride) {
       c.t_next = c.t_end - 1 + n;
       c.t_end = c.t_next + 1;
@@ -314,8 +322,21 @@ __device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t*
       ++p;
     }
   }
-  c.cur_t = t;
+  const uint64_t step = s.stride ? n : 1;
+  const uint64_t seen = s.pre_only ? s.pre_nt : (c.tot_seen > s.lookahead ? c.tot_seen - s.lookahead : 0);
+  const uint64_t end = c.base + c.nt < seen ? c.base + c.nt : seen;  // tickets below it need no look at the dispenser
+  uint32_t count = 1;
+  uint64_t last = t;
+  while (count < kTilesTogether && last + step < end && (s.stride || c.t_next < c.t_end)) {
+    last += step;
+    ++count;
+    c.t_next = last + 1;
+    if (s.stride) c.t_end = last + 1;
+  }
+  c.cur_t = last;
   *ti_out = (uint32_t)(t - c.base);
+  *count_out = count;
+  *step_out = (uint32_t)step;
   return true;
 }
 
@@ -482,7 +503,7 @@ __device__ void gather_copy(const SchedArgs& s, uint64_t off, uint32_t len) {
 // update while the other lanes keep passing the barriers, which never ends.
 template <class T>
 __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_persistent(T pay, SchedArgs s) {
-  __shared__ uint32_t sh_go, sh_p, sh_ti;
+  __shared__ uint32_t sh_go, sh_p, sh_ti, sh_count, sh_step;
   __shared__ uint64_t sh_g0, sh_g1;
   const bool wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x) == 0;
   const bool lane0 = threadIdx.x == 0;
@@ -615,17 +636,19 @@ __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_persisten
   for (;;) {
     if (wave0) {
       if (lane0) {
-        uint32_t p = 0, ti = 0;
+        uint32_t p = 0, ti = 0, count = 0, step = 0;
         uint64_t g0 = 0, g1 = 0;
         bool go;
         if (prev_p != 0xFFFFFFFFu) tile_finished(sa, c);
-        go = next_tile(pay, sa, c, &ti);
+        go = next_tile(pay, sa, c, &ti, &count, &step);
         p = c.p;
         g0 = c.g0;
         g1 = c.g1;
         sh_go = go ? 1u : 0u;
         sh_p = p;
         sh_ti = ti;
+        sh_count = count;
+        sh_step = step;
         sh_g0 = g0;
         sh_g1 = g1;
       }
@@ -635,6 +658,7 @@ __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_persisten
     if (go == 0) break;
     const uint32_t p = __builtin_amdgcn_readfirstlane(sh_p);
     const uint32_t ti = __builtin_amdgcn_readfirstlane(sh_ti);
+    const uint32_t count = __builtin_amdgcn_readfirstlane(sh_count), step = __builtin_amdgcn_readfirstlane(sh_step);
     const uint64_t g0 = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sh_g0 >> 32)) << 32) |
                         __builtin_amdgcn_readfirstlane((uint32_t)sh_g0);
     const uint64_t g1 = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sh_g1 >> 32)) << 32) |
@@ -644,9 +668,9 @@ __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_persisten
     // which count against the LDS counter too; with one pending, every LDS
     // wait inside the payload would have to drain all of them.
     __builtin_amdgcn_s_waitcnt(0);
-    pay.run(g0, g1, ti);
+    for (uint32_t k = 0; k < count; ++k) pay.run(g0, g1, ti + k * step);
     prev_p = p;
-    __syncthreads();  // the tile is complete and the shared slots may be reused
+    __syncthreads();  // the tiles are complete and the shared slots may be reused
   }
   if (wave0) {
     if (lane0) {
