@@ -25,6 +25,7 @@ struct EscapeTile {
   // residency of the plain launch, so that the 2048 tiles of a 1024 x 1024
   // grid run in one round
   static constexpr int kMinBlocksPerCu = 8;
+  static constexpr int kMaxBlocksPerCu = 8;
   ce_escape_params p;
   uint32_t* out;
   __device__ void load_constants() {}
@@ -84,14 +85,18 @@ __device__ __forceinline__ float dpp_from_right(float edge, float v) {
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // at any float's address
 
 // kFresh: the input may have been written after the launch began (the
 // serving kernel reuses memory while it runs), so wave-uniform reads, which
 // the compiler would serve from the scalar cache, use coherent vector loads.
 template <bool kFresh>
 struct Blur5TileT {
-  // five resident workgroups per CU keep enough loads in flight for HBM
+  // Five resident workgroups per CU keep enough loads in flight for HBM; in
+  // the plain launch of a large image seven are slower than six (16384^2:
+  // 450 against 424 us).
   static constexpr int kMinBlocksPerCu = 5;
+  static constexpr int kMaxBlocksPerCu = 6;
   ce_blur5_params p;
   const float* in;
   const float* wt;
@@ -115,7 +120,21 @@ struct Blur5TileT {
   __host__ __device__ uint32_t ncb() const { return (uint32_t)ceil_div(p.w, kBlurTileCols); }
   __host__ __device__ uint64_t granules() const { return p.h; }
   __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
-    return (uint32_t)(ceil_div(g1 - g0, kBlurTileRows) * ncb());
+    return (uint32_t)(ceil_div(g1 - g0, tile_rows()) * ncb());
+  }
+  // Rows of a tile: halved from 32 until the image has two tiles per compute
+  // unit, to no fewer than four, or two where even that leaves compute units
+  // without a tile. A wave's rows come one after another, a load's latency
+  // each, so short tiles are what a small image needs; a large one needs few
+  // halo rows (four per tile). Runs with at least 512, 1024 and 2048
+  // tiles asked for: 1024^2 (32 tiles of 32 rows) 25.0 us before, 15.4 with
+  // any; 2048^2 25.5 before, 19.1, 20.3, 20.0; 4096^2 34.9 before, 35.0, 36.0,
+  // 38.4; 3000 x 4000 41.0 before (also for its last columns), 30.2, 32.2,
+  // 35.9; 512^2 in two rows 14.3, in four 14.9, 1000^2 15.7 and 15.4.
+  __host__ __device__ uint32_t tile_rows() const {
+    uint32_t r = kBlurTileRows;
+    while (r > 2 && ceil_div(p.h, r) * ncb() < (r > 4 ? 512u : 192u)) r /= 2;
+    return r;
   }
   __device__ __forceinline__ const float* row_ptr(int64_t yy) const {
     yy = yy < 0 ? 0 : (yy >= (int64_t)p.h ? (int64_t)p.h - 1 : yy);
@@ -137,17 +156,18 @@ struct Blur5TileT {
     }
   }
 
-  // Fast path: the wave's 256 columns lie inside the image and rows are
-  // 16-byte aligned. Each lane loads its float4; the two columns on either
+  // Fast path: the wave's 256 columns lie inside the image (at any alignment:
+  // a 16-byte load needs four-byte alignment only). Each lane loads its
+  // float4; the two columns on either
   // side come from the neighbouring lanes by DPP, and the wave's outer halo
   // from four uniform (scalar) loads clamped to the image.
   struct Raw {
-    float4 c;
+    f32x4 c;
     float l0, l1, r0, r1;
   };
   __device__ __forceinline__ void load_raw(int64_t yy, uint32_t x, uint32_t xw, Raw& a) const {
     const float* row = row_ptr(yy);
-    a.c = *reinterpret_cast<const float4*>(row + x);
+    a.c = *reinterpret_cast<const f32x4u*>(row + x);
     a.l0 = uniform_load(row + (xw >= 2 ? xw - 2 : 0));
     a.l1 = uniform_load(row + (xw >= 1 ? xw - 1 : 0));
     a.r0 = uniform_load(row + (xw + 256 < p.w ? xw + 256 : p.w - 1));
@@ -187,13 +207,13 @@ struct Blur5TileT {
         // Streaming store: the output is not read again by this kernel, so
         // it should not push the input rows (reused as halo) out of L2.
         const f32x4 ov = {o[0], o[1], o[2], o[3]};
-        __builtin_nontemporal_store(ov, reinterpret_cast<f32x4*>(out + (size_t)y * p.w + x));
+        __builtin_nontemporal_store(ov, reinterpret_cast<f32x4u*>(out + (size_t)y * p.w + x));
       }
     }
   }
 
-  // General path (ragged widths, the wave holding the image's right edge when
-  // the width is not a multiple of 4): per-element clamped loads.
+  // General path (images narrower than a wave's 256 columns): per-element
+  // clamped loads.
   __device__ void load8(int64_t yy, uint32_t x, float v[8]) const {
     const float* row = row_ptr(yy);
 #pragma unroll
@@ -224,18 +244,24 @@ struct Blur5TileT {
   }
 
   __device__ void run(uint64_t g0, uint64_t g1, uint32_t t) const {
-    const uint32_t nc = ncb();
-    const uint64_t r0 = g0 + (uint64_t)(t / nc) * kBlurTileRows;
-    const uint64_t r1 = (r0 + kBlurTileRows < g1) ? r0 + kBlurTileRows : g1;
+    const uint32_t nc = ncb(), rows = tile_rows();
+    const uint64_t r0 = g0 + (uint64_t)(t / nc) * rows;
+    const uint64_t r1 = (r0 + rows < g1) ? r0 + rows : g1;
     // first column of this wave (uniform) and of this lane
     const uint32_t tid = thread_index();
     const uint32_t xw = (t % nc) * kBlurTileCols + (__builtin_amdgcn_readfirstlane(tid) & ~63u) * 4u;
-    const uint32_t x = xw + (tid & 63u) * 4u;
     if (xw >= p.w) return;
-    if ((p.w & 3u) == 0 && xw + 256 <= p.w)
-      run_fast(r0, r1, x, xw);
-    else
-      run_general(r0, r1, x);
+    if (p.w >= 256) {
+      // The wave at the right edge takes the last 256 columns: the ones it
+      // shares with its neighbour get the same values from both. With its own
+      // columns and per-element loads, and those for every wave where the
+      // width is no multiple of four, 4099 x 3001 took 96 us, now 33, and
+      // 8190 x 8192 444 us, now 101.
+      const uint32_t xs = xw + 256 <= p.w ? xw : p.w - 256;
+      run_fast(r0, r1, xs + (tid & 63u) * 4u, xs);
+    } else {
+      run_general(r0, r1, xw + (tid & 63u) * 4u);
+    }
   }
 };
 
@@ -468,6 +494,7 @@ template <bool STRICT>
 struct NbodyTile {
   // four workgroups per CU: four waves per SIMD, 128 registers each
   static constexpr int kMinBlocksPerCu = 4;
+  static constexpr int kMaxBlocksPerCu = 8;
   ce_nbody_params p;
   const float4* pos;
   float4* out;
@@ -514,6 +541,7 @@ struct NbodyTile {
 template <bool STRICT>
 struct NbodyStepTile {
   static constexpr int kMinBlocksPerCu = 4;
+  static constexpr int kMaxBlocksPerCu = 8;
   ce_nbody_step_params p;
   const float4* pos;
   const float4* vel;
@@ -596,6 +624,7 @@ __device__ __forceinline__ float binomial_leaf(float S, float f, float X) {
 // against a workgroup per pair of groups with a barrier at every level.
 struct BinomialTile {
   static constexpr int kMinBlocksPerCu = 8;
+  static constexpr int kMaxBlocksPerCu = 8;
   static constexpr uint32_t kGroupsPerTile = kBlockThreads / 64;
   ce_binomial_params p;
   const float4* spots;
@@ -690,6 +719,7 @@ struct BinomialTile {
 // about 190 (205), 8,192 188 (120): a wave takes 185 us however few there are.
 struct BinomialCallTile {
   static constexpr int kMinBlocksPerCu = 2;
+  static constexpr int kMaxBlocksPerCu = 8;
   static constexpr uint32_t kGroupsPerTile = kBlockThreads / 4;
   static constexpr int kLow = 192, kHigh = 64, kStep = 16;
   ce_binomial_params p;

@@ -722,8 +722,10 @@ __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_direct(T 
   if (lane0) sys_store(&d.wg_end[blockIdx.x], now_tick());
 }
 
+// (One workgroup of 256 threads is a wave on each SIMD of its compute unit.)
 template <class T>
-__global__ __launch_bounds__(kBlockThreads) void k_bare(T pay, uint64_t G) {
+__global__ __launch_bounds__(kBlockThreads)
+__attribute__((amdgpu_waves_per_eu(1, T::kMaxBlocksPerCu))) void k_bare(T pay, uint64_t G) {
   pay.load_constants();
   pay.run(0, G, blockIdx.x);
 }
