@@ -429,12 +429,15 @@ constexpr uint32_t kNbodyWhole = 256;
 
 template <bool STRICT>
 __device__ __forceinline__ f32x4 nbody_accumulate_whole(const f32x4* pos, uint32_t n, float eps2, uint32_t tid,
-                                                        const f32x4 pi, f32x4 (&sh)[kNbodyWhole]) {
+                                                        const f32x4 pi, f32x4 (&stages)[2 * kNbodyWhole]) {
   const NbodyTerms<STRICT> terms{eps2};
+  __syncthreads();  // the tile before may still be read
   f32x4 acc = {0.f, 0.f, 0.f, 0.f}, stage = pi;
   if (tid < n) stage = pos[tid];
   for (uint32_t j0 = 0; j0 < n; j0 += kNbodyWhole) {
-    __syncthreads();
+    // two stages in turn: the barrier before a stage's arithmetic also says
+    // that every wave is done with the stage before
+    f32x4* const sh = stages + (j0 & kNbodyWhole);
     sh[tid] = stage;
     __syncthreads();
     if (j0 + kNbodyWhole + tid < n) stage = pos[j0 + kNbodyWhole + tid];
@@ -470,17 +473,22 @@ __device__ __forceinline__ f32x4 nbody_accumulate_whole(const f32x4* pos, uint32
   return acc;
 }
 
-// Whether the engine's tiles are whole granules: with the strict 1/sqrt, where
-// the granules give (nearly) every one of the 256 compute units two, so two
-// waves per SIMD. At 131,072 bodies 6.88 ms against 7.35 in groups of 64, at
-// 122,880 6.26 against 6.77; with one and a half waves per SIMD (98,304) it is
-// 4.76 against 4.16, with three (196,608) 19.1 against 16.3, with four 28.5
-// against 28.3. With the hardware 1/sqrt the groups are always faster
-// (131,072: 5.26 against 5.63).
+// Whether the engine's tiles are whole granules: where those give most of the
+// 256 compute units two, so two waves per SIMD, and groups of 64, more than
+// six (hardware 1/sqrt: seven) per compute unit, a second round as full as the
+// first. Whole against groups, in ms, GPU alone and in packages of 256 bodies.
+// Strict 1/sqrt: 131,072 bodies 6.90 and 6.99 against 7.00 and 7.70; 118,000
+// 5.92 and 5.97 against 6.49 and 7.10; 110,000 5.39 and 5.44 against 5.27 and
+// 5.33 (on a slower card 5.6 and 5.6 against 5.54 and 5.71); 100,000 4.88 and
+// 4.93 against 4.86 and 4.92; 98,304 4.76 against 4.16 (alone). Hardware
+// 1/sqrt: 131,072 5.43 and 5.43 against 5.30 and 5.63; 118,000 4.89 and 4.88
+// against 4.82 and 5.14; 114,688 4.86 and 4.95 against 4.11 and 4.13. With
+// three or four granules per compute unit groups are faster or equal (strict,
+// 196,608: 16.3 against 19.1; 262,144: 28.3 against 28.5).
 template <bool STRICT>
 __host__ __device__ inline bool nbody_whole(uint32_t n) {
   const uint32_t granules = n / kNbodyGranule + (n % kNbodyGranule != 0);
-  return STRICT && granules > 464 && granules <= 512;
+  return granules > (STRICT ? 384u : 448u) && granules <= 512u;
 }
 
 // Tiles of a range of 256-body granules in groups of 64 bodies.
@@ -504,7 +512,7 @@ struct NbodyTile {
     return nbody_whole<STRICT>(p.n) ? (uint32_t)(g1 - g0) : nbody_tiles(p.n, g0, g1);
   }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    if (STRICT && nbody_whole<STRICT>(p.n))
+    if (nbody_whole<STRICT>(p.n))
       run_whole(g0, t);
     else
       run_group<kBlockThreads / 64, kNbodyChunk>(g0, t);
@@ -521,7 +529,7 @@ struct NbodyTile {
     if (nbody_accumulate<STRICT, kWaves, kChunk>(p4, p.n, p.eps2, lane, pi, sh, a) && active) store(i, a);
   }
   __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
-    __shared__ f32x4 sh[kNbodyWhole];
+    __shared__ f32x4 sh[2 * kNbodyWhole];
     const uint32_t tid = thread_index();
     const uint64_t i = (g0 + t) * kNbodyGranule + tid;
     const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
@@ -553,7 +561,7 @@ struct NbodyStepTile {
     return nbody_whole<STRICT>(p.n) ? (uint32_t)(g1 - g0) : nbody_tiles(p.n, g0, g1);
   }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    if (STRICT && nbody_whole<STRICT>(p.n))
+    if (nbody_whole<STRICT>(p.n))
       run_whole(g0, t);
     else
       run_group<kBlockThreads / 64, kNbodyChunk>(g0, t);
@@ -570,7 +578,7 @@ struct NbodyStepTile {
     if (nbody_accumulate<STRICT, kWaves, kChunk>(p4, p.n, p.eps2, lane, pi, sh, a) && active) store(i, pi, a);
   }
   __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
-    __shared__ f32x4 sh[kNbodyWhole];
+    __shared__ f32x4 sh[2 * kNbodyWhole];
     const uint32_t tid = thread_index();
     const uint64_t i = (g0 + t) * kNbodyGranule + tid;
     const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);

@@ -1126,7 +1126,13 @@ struct ce_engine {
         grid = grid_override + gather_wgs;
       } else {
         const uint64_t r = std::max<uint64_t>(1, resident - gather_wgs);
-        grid = balanced_grid(all_tiles, r, (uint64_t)std::max(1, n_cu)) + gather_wgs;
+        // N-body: as many workgroups as are resident. Its tiles are long and
+        // bound by issue, which several workgroups of a compute unit fill and
+        // one does not, so whole rounds of fewer workgroups lose (77,578
+        // bodies, 1213 tiles: five rounds of 256 took 5.0 ms, one workgroup
+        // per tile 2.8).
+        grid = (uint32_t)(is_nbody() ? std::min(all_tiles, r) : balanced_grid(all_tiles, r, (uint64_t)std::max(1, n_cu))) +
+               gather_wgs;
       }
       if (grid <= gather_wgs) grid = gather_wgs + 1;
     }
@@ -1328,8 +1334,9 @@ struct ce_engine {
         // plain launch is. A fixed split over fewer workgroups keeps fewer
         // of them per CU than the hardware would (blur 16384^2: 1024
         // workgroups of eight tiles ran 2.8 % longer than 8192 of one).
-        if (!grid_override && !sweep && gs.pre_nt >= kDirectOneShotRounds * (uint64_t)resident_wgs &&
-            gs.pre_nt <= kFastExitMaxWgs)
+        // N-body tiles, long and few, from one round on.
+        if (!grid_override && !sweep &&
+            gs.pre_nt >= (is_nbody() ? 1 : kDirectOneShotRounds) * (uint64_t)resident_wgs && gs.pre_nt <= kFastExitMaxWgs)
           grid = gs.pre_nt;
         if (uneven_one_shot) {
           grid = gs.pre_nt;

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 EPS2 = 1e-6
 SIZES = [1, 2, 7, 8, 9, 23, 24, 25, 47, 48, 49, 63, 64, 65, 95, 96, 97, 191, 192, 193, 255, 256, 257, 383, 384, 385,
          767, 768, 769, 1000]
-BORDERS = [16384, 16385, 32767, 32768, 118784, 118785, 131072, 131073]
+BORDERS = [16384, 16385, 32767, 32768, 98304, 98305, 114688, 114689, 131072, 131073]
 
 
 @pytest.fixture(scope="module")
