@@ -298,6 +298,14 @@ struct NbodyShared {
   uint32_t turn;
 };
 
+// The forms of one kernel share their LDS: four workgroups of a compute unit
+// have 160 KB between them.
+template <uint32_t kBytes>
+__device__ __forceinline__ unsigned char* nbody_lds() {
+  __shared__ __align__(16) unsigned char lds[kBytes];
+  return lds;
+}
+
 // A zero that the compiler does not keep in registers over the tile loop.
 __device__ __forceinline__ float fresh_zero() {
   float x = 0.0f;
@@ -473,6 +481,136 @@ __device__ __forceinline__ f32x4 nbody_accumulate_whole(const f32x4* pos, uint32
   return acc;
 }
 
+// The same acceleration for few bodies, where the chain of the sums bounds the
+// run: a tile of 16 bodies, one wave that only adds and kWaves - 1 that work out
+// the terms. Those write (dx, dy, dz, f) of kChunk bodies j each and phase into
+// LDS; in the adding wave a lane is one component of one body, reads one float
+// per j and takes f from its neighbour (lane 3 of four) by DPP, so a sum costs
+// one instruction per j instead of three, and nothing is handed on. Three phases
+// of the ring: one being written, one complete, whose first half is read before
+// the barrier, one being added. The bodies past n are padded with d = -0, f = 0,
+// which leave a sum as it is, its sign and a NaN included.
+//
+// An addition takes 11 to 12 cycles (8 to 9 of them the latency of the fma), the
+// relay above 22. 4,096 bodies, strict, a whole call of the GPU alone: 38 us, with
+// the wide groups 49; in packages of 256 bodies 67 against 82.
+constexpr uint32_t kNbodyFeedGroup = 16;
+constexpr uint32_t kNbodyFeedChunk = 16;  // of a 256-thread workgroup
+// Two tiles per compute unit, where it is no slower than groups of 64 for the GPU
+// alone (8,192 bodies, strict: 83.8 us against 84.6) and faster in packages (117
+// against 139); beyond, the terms bound the run and groups work them out with
+// fewer instructions (12,000: kernel alone 125 us against about 108).
+constexpr uint32_t kNbodyFeedMax = 8192;
+
+template <uint32_t kWaves, uint32_t kChunk>
+struct NbodyRing {
+  static constexpr uint32_t kPhase = (kWaves - 1) * kChunk;
+  f32x4 term[3][kPhase][kNbodyFeedGroup];
+};
+constexpr uint32_t kNbodyLds = sizeof(NbodyRing<kBlockThreads / 64, kNbodyFeedChunk>);  // the largest
+
+// sum += f d, twelve or four j after one another. One block, as the compiler
+// puts a wait or an s_nop between any two. The s_nop is the distance that a DPP
+// operand needs from a vector instruction that writes it.
+#define CE_NBODY_FMAC(k) "v_fmac_f32_dpp %0, %" #k ", %" #k " quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+template <int kCount>
+__device__ __forceinline__ void nbody_sum(float& a, const float* v) {
+  if constexpr (kCount >= 12) {
+    asm("s_nop 1\n\t" CE_NBODY_FMAC(1) CE_NBODY_FMAC(2) CE_NBODY_FMAC(3) CE_NBODY_FMAC(4) CE_NBODY_FMAC(5)
+            CE_NBODY_FMAC(6) CE_NBODY_FMAC(7) CE_NBODY_FMAC(8) CE_NBODY_FMAC(9) CE_NBODY_FMAC(10) CE_NBODY_FMAC(11)
+                CE_NBODY_FMAC(12)
+        : "+v"(a)
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]), "v"(v[8]), "v"(v[9]),
+          "v"(v[10]), "v"(v[11]));
+    nbody_sum<kCount - 12>(a, v + 12);
+  } else if constexpr (kCount > 0) {
+    static_assert(kCount >= 4, "batches of twelve and four");
+    asm("s_nop 1\n\t" CE_NBODY_FMAC(1) CE_NBODY_FMAC(2) CE_NBODY_FMAC(3) CE_NBODY_FMAC(4)
+        : "+v"(a)
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+    nbody_sum<kCount - 4>(a, v + 4);
+  }
+}
+#undef CE_NBODY_FMAC
+
+// The sums of the 16 bodies from b0 on: true in the adding wave, whose lane l
+// returns component l & 3 of body b0 + (l >> 2) (l & 3 == 3: any value).
+template <bool STRICT, uint32_t kWaves, uint32_t kChunk>
+__device__ __forceinline__ bool nbody_feed(const f32x4* pos, uint32_t n, float eps2, uint32_t b0, uint32_t lane,
+                                           NbodyRing<kWaves, kChunk>& ring, float& sum) {
+  constexpr uint32_t kPhase = NbodyRing<kWaves, kChunk>::kPhase, kHalf = kPhase / 2, kSteps = kChunk / 4;
+  constexpr uint32_t kSlotFloats = kPhase * kNbodyFeedGroup * 4;
+  static_assert(kChunk % 8 == 0, "whole steps of four j, halves of whole batches");
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t phases = n / kPhase + (n % kPhase != 0);
+  // Every wave passes phases + 3 barriers.
+  __syncthreads();  // the tile before is done with `ring`
+  if (w == 0) {
+    __builtin_amdgcn_s_setprio(3);  // the other waves wait for this chain
+    const float* const base = reinterpret_cast<const float*>(&ring) + lane;
+    const float* cur = base;
+    float a[kHalf], b[kHalf];
+    sum = fresh_zero();
+    __syncthreads();
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < kHalf; ++k) a[k] = cur[k * 64];
+    uint32_t slot = 0;
+#pragma unroll 1
+    for (uint32_t p = 0; p < phases; ++p) {
+#pragma unroll
+      for (uint32_t k = 0; k < kHalf; ++k) b[k] = cur[(kHalf + k) * 64];
+      __builtin_amdgcn_sched_barrier(0);
+      nbody_sum<kHalf>(sum, a);
+      __builtin_amdgcn_sched_barrier(0);
+      slot = slot == 2 ? 0 : slot + 1;
+      cur = base + slot * kSlotFloats;
+#pragma unroll
+      for (uint32_t k = 0; k < kHalf; ++k) a[k] = cur[k * 64];  // unused past the last phase
+      __builtin_amdgcn_sched_barrier(0);
+      nbody_sum<kHalf>(sum, b);
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();
+    }
+    __builtin_amdgcn_s_setprio(0);
+    return true;
+  }
+  const NbodyTerms<STRICT> terms{eps2};
+  const uint32_t body = lane & 15u, i = b0 + body, j0 = (w - 1) * kChunk + (lane >> 4);
+  const f32x4 pi = pos[i < n ? i : n - 1];
+  const auto load = [&](uint32_t p, f32x4(&x)[kSteps]) {
+#pragma unroll
+    for (uint32_t k = 0; k < kSteps; ++k) {
+      const uint32_t j = p * kPhase + j0 + k * 4;
+      x[k] = pos[j < n ? j : n - 1];
+    }
+  };
+  uint32_t slot = 0, p = 0;
+  // a phase's terms, and the bodies of the phase after the next
+  const auto feed = [&](f32x4(&x)[kSteps]) {
+#pragma unroll
+    for (uint32_t k = 0; k < kSteps; ++k) {
+      f32x4 t = terms(x[k], pi);
+      if ((p + 1) * kPhase > n && p * kPhase + j0 + k * 4 >= n) t = f32x4{-0.0f, -0.0f, -0.0f, 0.0f};
+      ring.term[slot][j0 + k * 4][body] = t;
+    }
+    load(p + 2, x);
+    slot = slot == 2 ? 0 : slot + 1;
+    ++p;
+    __syncthreads();
+  };
+  f32x4 x0[kSteps], x1[kSteps];
+  load(0, x0);
+  load(1, x1);
+#pragma unroll 1
+  while (p + 2 <= phases + 2) {
+    feed(x0);
+    feed(x1);
+  }
+  if (p < phases + 2) feed(x0);
+  return false;
+}
+
 // Whether the engine's tiles are whole granules: where those give most of the
 // 256 compute units two, so two waves per SIMD, and groups of 64, more than
 // six (hardware 1/sqrt: seven) per compute unit, a second round as full as the
@@ -491,10 +629,15 @@ __host__ __device__ inline bool nbody_whole(uint32_t n) {
   return granules > (STRICT ? 384u : 448u) && granules <= 512u;
 }
 
-// Tiles of a range of 256-body granules in groups of 64 bodies.
-__host__ __device__ inline uint32_t nbody_tiles(uint32_t n, uint64_t g0, uint64_t g1) {
+// Tiles of a range of 256-body granules in groups of `group` bodies.
+__host__ __device__ inline uint32_t nbody_tiles(uint32_t n, uint64_t g0, uint64_t g1, uint32_t group = kNbodyGroup) {
   const uint64_t end = g1 * kNbodyGranule < n ? g1 * kNbodyGranule : n;
-  return g0 * kNbodyGranule < end ? (uint32_t)ceil_div(end - g0 * kNbodyGranule, kNbodyGroup) : 0;
+  return g0 * kNbodyGranule < end ? (uint32_t)ceil_div(end - g0 * kNbodyGranule, group) : 0;
+}
+template <bool STRICT>
+__host__ __device__ inline uint32_t nbody_engine_tiles(uint32_t n, uint64_t g0, uint64_t g1) {
+  return nbody_whole<STRICT>(n) ? (uint32_t)(g1 - g0)
+                                : nbody_tiles(n, g0, g1, n <= kNbodyFeedMax ? kNbodyFeedGroup : kNbodyGroup);
 }
 
 // Accelerations: a granule is 256 bodies, a tile 64 of them or all.
@@ -509,17 +652,20 @@ struct NbodyTile {
   __device__ void load_constants() {}
   __host__ __device__ uint64_t granules() const { return ceil_div(p.n, kNbodyGranule); }
   __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
-    return nbody_whole<STRICT>(p.n) ? (uint32_t)(g1 - g0) : nbody_tiles(p.n, g0, g1);
+    return nbody_engine_tiles<STRICT>(p.n, g0, g1);
   }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    if (nbody_whole<STRICT>(p.n))
+    if (p.n <= kNbodyFeedMax)
+      run_feed<kBlockThreads / 64, kNbodyFeedChunk, kNbodyLds>(g0, t);
+    else if (nbody_whole<STRICT>(p.n))
       run_whole(g0, t);
     else
-      run_group<kBlockThreads / 64, kNbodyChunk>(g0, t);
+      run_group<kBlockThreads / 64, kNbodyChunk, kNbodyLds>(g0, t);
   }
-  template <uint32_t kWaves, uint32_t kChunk>
+  template <uint32_t kWaves, uint32_t kChunk, uint32_t kLds = sizeof(NbodyShared<kWaves, kChunk>)>
   __device__ __forceinline__ void run_group(uint64_t g0, uint32_t t) const {
-    __shared__ NbodyShared<kWaves, kChunk> sh;
+    static_assert(sizeof(NbodyShared<kWaves, kChunk>) <= kLds, "");
+    auto& sh = *reinterpret_cast<NbodyShared<kWaves, kChunk>*>(nbody_lds<kLds>());
     const uint32_t lane = thread_index() & 63u;
     const uint64_t i = g0 * kNbodyGranule + (uint64_t)t * kNbodyGroup + lane;
     const bool active = i < p.n;
@@ -528,14 +674,30 @@ struct NbodyTile {
     f32x4 a;
     if (nbody_accumulate<STRICT, kWaves, kChunk>(p4, p.n, p.eps2, lane, pi, sh, a) && active) store(i, a);
   }
+  template <uint32_t kWaves, uint32_t kChunk, uint32_t kLds = sizeof(NbodyRing<kWaves, kChunk>)>
+  __device__ __forceinline__ void run_feed(uint64_t g0, uint32_t t) const {
+    auto& ring = *reinterpret_cast<NbodyRing<kWaves, kChunk>*>(nbody_lds<kLds>());
+    const uint32_t b0 = (uint32_t)(g0 * kNbodyGranule) + t * kNbodyFeedGroup;
+    const uint32_t lane = thread_index() & 63u;
+    float a;
+    if (nbody_feed<STRICT, kWaves, kChunk>(reinterpret_cast<const f32x4*>(pos), p.n, p.eps2, b0, lane, ring, a)) {
+      const uint32_t k = b0 * 4 + (thread_index() & 63u);
+      if (k < p.n * 4) store_component(k, a);
+    }
+  }
   __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
-    __shared__ f32x4 sh[2 * kNbodyWhole];
+    static_assert(sizeof(f32x4[2 * kNbodyWhole]) <= kNbodyLds, "");
+    auto& sh = *reinterpret_cast<f32x4(*)[2 * kNbodyWhole]>(nbody_lds<kNbodyLds>());
     const uint32_t tid = thread_index();
     const uint64_t i = (g0 + t) * kNbodyGranule + tid;
     const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
     const f32x4 pi = i < p.n ? p4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
     const f32x4 a = nbody_accumulate_whole<STRICT>(p4, p.n, p.eps2, tid, pi, sh);
     if (i < p.n) store((g0 + t) * kNbodyGranule + thread_index(), a);
+  }
+  // float k of the output
+  __device__ __forceinline__ void store_component(uint32_t k, float a) const {
+    reinterpret_cast<float*>(out)[k] = (k & 3u) == 3u ? 0.0f : a;
   }
   __device__ __forceinline__ void store(uint64_t i, const f32x4 a) const {
     out[i] = make_float4(a.x, a.y, a.z, 0.0f);
@@ -558,17 +720,20 @@ struct NbodyStepTile {
   __device__ void load_constants() {}
   __host__ __device__ uint64_t granules() const { return ceil_div(p.n, kNbodyGranule); }
   __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
-    return nbody_whole<STRICT>(p.n) ? (uint32_t)(g1 - g0) : nbody_tiles(p.n, g0, g1);
+    return nbody_engine_tiles<STRICT>(p.n, g0, g1);
   }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    if (nbody_whole<STRICT>(p.n))
+    if (p.n <= kNbodyFeedMax)
+      run_feed<kBlockThreads / 64, kNbodyFeedChunk, kNbodyLds>(g0, t);
+    else if (nbody_whole<STRICT>(p.n))
       run_whole(g0, t);
     else
-      run_group<kBlockThreads / 64, kNbodyChunk>(g0, t);
+      run_group<kBlockThreads / 64, kNbodyChunk, kNbodyLds>(g0, t);
   }
-  template <uint32_t kWaves, uint32_t kChunk>
+  template <uint32_t kWaves, uint32_t kChunk, uint32_t kLds = sizeof(NbodyShared<kWaves, kChunk>)>
   __device__ __forceinline__ void run_group(uint64_t g0, uint32_t t) const {
-    __shared__ NbodyShared<kWaves, kChunk> sh;
+    static_assert(sizeof(NbodyShared<kWaves, kChunk>) <= kLds, "");
+    auto& sh = *reinterpret_cast<NbodyShared<kWaves, kChunk>*>(nbody_lds<kLds>());
     const uint32_t lane = thread_index() & 63u;
     const uint64_t i = g0 * kNbodyGranule + (uint64_t)t * kNbodyGroup + lane;
     const bool active = i < p.n;
@@ -577,14 +742,34 @@ struct NbodyStepTile {
     f32x4 a;
     if (nbody_accumulate<STRICT, kWaves, kChunk>(p4, p.n, p.eps2, lane, pi, sh, a) && active) store(i, pi, a);
   }
+  template <uint32_t kWaves, uint32_t kChunk, uint32_t kLds = sizeof(NbodyRing<kWaves, kChunk>)>
+  __device__ __forceinline__ void run_feed(uint64_t g0, uint32_t t) const {
+    auto& ring = *reinterpret_cast<NbodyRing<kWaves, kChunk>*>(nbody_lds<kLds>());
+    const uint32_t b0 = (uint32_t)(g0 * kNbodyGranule) + t * kNbodyFeedGroup;
+    const uint32_t lane = thread_index() & 63u;
+    float a;
+    if (nbody_feed<STRICT, kWaves, kChunk>(reinterpret_cast<const f32x4*>(pos), p.n, p.eps2, b0, lane, ring, a)) {
+      const uint32_t k = b0 * 4 + (thread_index() & 63u);
+      if (k < p.n * 4) store_component(k, a);
+    }
+  }
   __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
-    __shared__ f32x4 sh[2 * kNbodyWhole];
+    static_assert(sizeof(f32x4[2 * kNbodyWhole]) <= kNbodyLds, "");
+    auto& sh = *reinterpret_cast<f32x4(*)[2 * kNbodyWhole]>(nbody_lds<kNbodyLds>());
     const uint32_t tid = thread_index();
     const uint64_t i = (g0 + t) * kNbodyGranule + tid;
     const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
     const f32x4 pi = i < p.n ? p4[i] : f32x4{0.f, 0.f, 0.f, 0.f};
     const f32x4 a = nbody_accumulate_whole<STRICT>(p4, p.n, p.eps2, tid, pi, sh);
     if (i < p.n) store((g0 + t) * kNbodyGranule + thread_index(), pi, a);
+  }
+  __device__ __forceinline__ void store_component(uint32_t k, float a) const {
+    const float x = reinterpret_cast<const float*>(pos)[k], v = reinterpret_cast<const float*>(vel)[k];
+    const float dt = p.dt;
+    const float h = (dt * dt) * 0.5f;
+    const bool copy = (k & 3u) == 3u;
+    reinterpret_cast<float*>(pos_out)[k] = copy ? x : (x + v * dt) + a * h;
+    reinterpret_cast<float*>(vel_out)[k] = copy ? v : v + a * dt;
   }
   __device__ __forceinline__ void store(uint64_t i, const f32x4 pi, const f32x4 a) const {
     const float4 vi = vel[i];

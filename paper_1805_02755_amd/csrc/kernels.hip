@@ -102,13 +102,13 @@ __global__ __launch_bounds__(kBlockThreads, EscapeTile::kMinBlocksPerCu) void k_
   if (first) sys_store(&d.wg_end[blockIdx.x], now_tick());
 }
 
-// N-body tiles that do not fill the GPU: eight waves per group of 64 bodies
+// N-body tiles of 64 that do not fill the GPU: eight waves per group of 64 bodies
 // and chunks of 48, one workgroup of 256 registers per compute unit. There the
 // chain of the sums bounds the run (15.4 cycles of issue per interaction and
 // about 250 to hand the sums on, per chunk), so longer chunks and more waves
 // that work out terms pay; where several tiles share a compute unit, other
 // tiles fill the waits, and the four waves of 24 keep more of them resident.
-// 4,096 bodies, strict: 38 us against 64 us, 16,384: 139 against 245; 30,001
+// 16,384 bodies, strict: 139 us against 245; 30,001
 // (469 tiles) with the hardware 1/sqrt: 428 against 365.
 constexpr uint32_t kWideThreads = 512;
 constexpr uint32_t kWideChunk = 48;
@@ -129,6 +129,27 @@ __global__ __launch_bounds__(kWideThreads, 2) void k_wide(T pay, DirectArgs d) {
   if (threadIdx.x == 0) sys_store(&d.wg_end[blockIdx.x], now_tick());
 }
 
+// N-body tiles of 16 bodies with seven waves that work out terms: two waves per
+// SIMD keep ahead of the adding wave (4,096 bodies, strict, kernel alone: 26 us
+// against 36 with the three of a 256-thread workgroup, hardware 1/sqrt 24
+// against 28).
+constexpr uint32_t kFeedThreads = 512;
+constexpr uint32_t kFeedChunk = 8;
+
+template <class T>
+__global__ __launch_bounds__(kFeedThreads, 4) void k_feed(T pay, DirectArgs d) {
+  if (d.wg_end && blockIdx.x == 0 && threadIdx.x == 0) {
+    const uint64_t tp = now_tick();
+    dev_store(&d.pkgs[0].t_claim, tp);
+    sys_store(&d.l1->gpu_t_first, tp);
+  }
+  for (uint32_t t = blockIdx.x; t < d.ntiles; t += gridDim.x)
+    pay.template run_feed<kFeedThreads / 64, kFeedChunk>(d.g0, t);
+  if (!d.wg_end) return;
+  __syncthreads();
+  if (threadIdx.x == 0) sys_store(&d.wg_end[blockIdx.x], now_tick());
+}
+
 // ------------------------------------------------------------ host helpers
 namespace {
 // The sweep's workgroups: one round of resident ones, two from 65,536 blocks
@@ -143,17 +164,21 @@ uint32_t sweep_workgroups(uint32_t planned, uint64_t blocks) {
 }
 template <class T>
 void launch_nbody_direct(const T& pay, const DirectArgs& d, uint32_t grid, hipStream_t st) {
-  if (d.ntiles <= kWideMaxTiles)
+  if (pay.p.n <= kNbodyFeedMax)
+    hipLaunchKernelGGL(k_feed<T>, dim3(grid), dim3(kFeedThreads), 0, st, pay, d);
+  else if (d.ntiles <= kWideMaxTiles)
     hipLaunchKernelGGL(k_wide<T>, dim3(grid), dim3(kWideThreads), 0, st, pay, d);
   else
     hipLaunchKernelGGL(k_direct<T>, dim3(grid), dim3(kBlockThreads), 0, st, pay, d);
 }
 template <class T>
 void launch_nbody_bare(const T& pay, uint64_t G, uint32_t tiles, hipStream_t st) {
-  if (tiles <= kWideMaxTiles) {
-    DirectArgs d{};
-    d.g1 = G;
-    d.ntiles = tiles;
+  DirectArgs d{};
+  d.g1 = G;
+  d.ntiles = tiles;
+  if (pay.p.n <= kNbodyFeedMax) {
+    hipLaunchKernelGGL(k_feed<T>, dim3(tiles), dim3(kFeedThreads), 0, st, pay, d);
+  } else if (tiles <= kWideMaxTiles) {
     hipLaunchKernelGGL(k_wide<T>, dim3(tiles), dim3(kWideThreads), 0, st, pay, d);
   } else {
     hipLaunchKernelGGL(k_bare<T>, dim3(tiles), dim3(kBlockThreads), 0, st, pay, G);

@@ -1,7 +1,8 @@
-"""N-body sizes where the handing-on of the sums could go wrong: around a chunk
-(8, 24, 48 bodies), a round of chunks over a workgroup's waves, a group of 64
-bodies, a granule, and the borders between the forms (wide groups, groups,
-whole granules); in the direct, persistent, plain and serving kernels. The
+"""N-body sizes where the order of the sums could go wrong: around a chunk (8,
+24, 48 bodies) and a round of chunks over a workgroup's waves, a phase of the
+terms fed to an adding wave (48, 56), a group of 16 or 64 bodies, a granule, and
+the borders between the forms (fed groups, wide groups, groups, whole granules);
+in the direct, persistent, plain and serving kernels. The
 strict form equals the oracle bit for bit; the hardware 1/sqrt lies within
 1e-5 of the sum of the terms' lengths."""
 import numpy as np
@@ -16,9 +17,9 @@ from gpu_util import DEV
 
 pytestmark = pytest.mark.gpu
 EPS2 = 1e-6
-SIZES = [1, 2, 7, 8, 9, 23, 24, 25, 47, 48, 49, 63, 64, 65, 95, 96, 97, 191, 192, 193, 255, 256, 257, 383, 384, 385,
-         767, 768, 769, 1000]
-BORDERS = [16384, 16385, 32767, 32768, 98304, 98305, 114688, 114689, 131072, 131073]
+SIZES = [1, 2, 7, 8, 9, 23, 24, 25, 47, 48, 49, 55, 56, 57, 63, 64, 65, 95, 96, 97, 111, 112, 113,
+         167, 168, 169, 191, 192, 193, 255, 256, 257, 383, 384, 385, 767, 768, 769, 1000]
+BORDERS = [8192, 8193, 8207, 8208, 8209, 16384, 16385, 32767, 32768, 98304, 98305, 114688, 114689, 131072, 131073]
 
 
 @pytest.fixture(scope="module")
