@@ -298,8 +298,8 @@ struct NbodyShared {
   uint32_t turn;
 };
 
-// The forms of one kernel share their LDS: four workgroups of a compute unit
-// have 160 KB between them.
+// The forms of one kernel share their LDS: the four or five workgroups of a
+// compute unit have 160 KB between them.
 template <uint32_t kBytes>
 __device__ __forceinline__ unsigned char* nbody_lds() {
   __shared__ __align__(16) unsigned char lds[kBytes];
@@ -658,7 +658,7 @@ struct NbodyTile {
     if (p.n <= kNbodyFeedMax)
       run_feed<kBlockThreads / 64, kNbodyFeedChunk, kNbodyLds>(g0, t);
     else if (nbody_whole<STRICT>(p.n))
-      run_whole(g0, t);
+      run_whole<kNbodyLds>(g0, t);
     else
       run_group<kBlockThreads / 64, kNbodyChunk, kNbodyLds>(g0, t);
   }
@@ -685,9 +685,10 @@ struct NbodyTile {
       if (k < p.n * 4) store_component(k, a);
     }
   }
+  template <uint32_t kLds>
   __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
-    static_assert(sizeof(f32x4[2 * kNbodyWhole]) <= kNbodyLds, "");
-    auto& sh = *reinterpret_cast<f32x4(*)[2 * kNbodyWhole]>(nbody_lds<kNbodyLds>());
+    static_assert(sizeof(f32x4[2 * kNbodyWhole]) <= kLds, "");
+    auto& sh = *reinterpret_cast<f32x4(*)[2 * kNbodyWhole]>(nbody_lds<kLds>());
     const uint32_t tid = thread_index();
     const uint64_t i = (g0 + t) * kNbodyGranule + tid;
     const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);
@@ -726,7 +727,7 @@ struct NbodyStepTile {
     if (p.n <= kNbodyFeedMax)
       run_feed<kBlockThreads / 64, kNbodyFeedChunk, kNbodyLds>(g0, t);
     else if (nbody_whole<STRICT>(p.n))
-      run_whole(g0, t);
+      run_whole<kNbodyLds>(g0, t);
     else
       run_group<kBlockThreads / 64, kNbodyChunk, kNbodyLds>(g0, t);
   }
@@ -753,9 +754,10 @@ struct NbodyStepTile {
       if (k < p.n * 4) store_component(k, a);
     }
   }
+  template <uint32_t kLds>
   __device__ __forceinline__ void run_whole(uint64_t g0, uint32_t t) const {
-    static_assert(sizeof(f32x4[2 * kNbodyWhole]) <= kNbodyLds, "");
-    auto& sh = *reinterpret_cast<f32x4(*)[2 * kNbodyWhole]>(nbody_lds<kNbodyLds>());
+    static_assert(sizeof(f32x4[2 * kNbodyWhole]) <= kLds, "");
+    auto& sh = *reinterpret_cast<f32x4(*)[2 * kNbodyWhole]>(nbody_lds<kLds>());
     const uint32_t tid = thread_index();
     const uint64_t i = (g0 + t) * kNbodyGranule + tid;
     const f32x4* const p4 = reinterpret_cast<const f32x4*>(pos);

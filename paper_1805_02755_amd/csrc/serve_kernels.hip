@@ -27,15 +27,16 @@ constexpr uint32_t kDescWords = sizeof(ServeDesc) / 8;
 // kernel four workgroups per compute unit instead of five.
 constexpr uint32_t kServeWholeBodies = 32768;
 constexpr uint32_t kServeNbodyChunk = 8;
+constexpr uint32_t kServeNbodyLds = sizeof(f32x4[2 * kNbodyWhole]);
 
 template <bool STRICT>
 __device__ void serve_nbody(const ServeDesc& d, uint32_t ti) {
   const ce_nbody_params nb{(uint32_t)__builtin_amdgcn_readfirstlane(d.nb.n), d.nb.eps2, d.nb.strict};
   const NbodyTile<STRICT> t{nb, (const float4*)d.in0, (float4*)d.out};
   if (nb.n >= kServeWholeBodies)  // uniform: both forms hold barriers
-    t.run_whole(0, ti);
+    t.template run_whole<kServeNbodyLds>(0, ti);
   else
-    t.template run_group<kBlockThreads / 64, kServeNbodyChunk>(0, ti);
+    t.template run_group<kBlockThreads / 64, kServeNbodyChunk, kServeNbodyLds>(0, ti);
 }
 
 __device__ __forceinline__ uint64_t sys_load_c(const uint64_t* p) { return sys_load(const_cast<uint64_t*>(p)); }
