@@ -43,6 +43,34 @@ def test_counts_equal_the_oracles(region, max_iter):
     assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
 
 
+# Around the discs that no orbit leaves: the fixed point's border at c = 1/4, at
+# -3/4 (where the cycle of two takes over) and in between, the cycle's at -5/4
+# and above, and the seahorse and elephant valleys, where orbits escape late.
+DISCS = {
+    "root": (0.2499, -3e-4, 4e-6, 6e-6),
+    "root_wide": (0.15, -0.12, 0.002, 0.0025),
+    "neck": (-0.7512, -0.0031, 2e-5, 6e-5),
+    "neck_wide": (-0.85, -0.12, 0.0015, 0.0025),
+    "two_left": (-1.2512, -0.002, 2e-5, 4e-5),
+    "two_top": (-1.02, 0.23, 3e-4, 4e-4),
+    "cusp_side": (0.27, 0.48, 2e-4, 2e-4),
+    "elephant": (0.255, 0.0, 2e-5, 2e-5),
+    "real_axis": (-2.0, 0.0, 0.018, 0.0),
+}
+
+
+@pytest.mark.parametrize("max_iter", [64, 20011])
+@pytest.mark.parametrize("region", sorted(DISCS))
+def test_orbits_near_the_discs(region, max_iter):
+    w, h = 128, 96
+    x0, y0, dx, dy = (float(np.float32(v)) for v in DISCS[region])
+    out = torch.full((h, w), -1, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    ce.ce_bare_run(ce.CE_KERNEL_ESCAPE, ce.ce_escape_params(w, h, x0, y0, dx, dy, max_iter), [], out)
+    ref = O.escape(w, h, x0, y0, dx, dy, max_iter)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), ref)
+
+
 @pytest.mark.parametrize("w,h", [(1, 1), (1, 700), (15, 3), (16, 4), (17, 5), (131, 96), (513, 33), (1025, 301),
                                  (4100, 67)])
 def test_every_pixel_once_however_the_blocks_are_dealt(w, h):
