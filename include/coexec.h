@@ -394,15 +394,16 @@ void ce_engine_clear_errors(ce_engine* e);
  * Many escape-time jobs of uneven sizes run as ONE persistent kernel launch
  * over the concatenation of their tiles, captured once in a hipGraph and
  * replayed, instead of one launch per job. The tile shape (tile_rows x
- * tile_cols, 256 pixels) and the tiles taken per workgroup request
- * (package_tiles, a Dynamic schedule inside the GPU, section 5.3) are chosen
+ * tile_cols, 256 pixels) and the tiles of a package (package_tiles; packages are
+ * dealt to the workgroups in claims of one or more, a Dynamic schedule inside
+ * the GPU, section 5.3) are chosen
  * by ce_batch_tune, which times every candidate on the batch itself. The
  * per-pixel arithmetic is that of CE_KERNEL_ESCAPE. GPU only. */
 typedef struct ce_batch ce_batch;
 typedef struct {
   uint32_t tile_rows;     /* 1, 2, 4, 8 or 16; tile_cols = 256 / tile_rows */
   uint32_t tile_cols;     /* output of ce_batch_get_config / ce_batch_tune  */
-  uint32_t package_tiles; /* tiles per workgroup request, >= 1              */
+  uint32_t package_tiles; /* consecutive tiles dealt together, >= 1         */
 } ce_batch_config;
 typedef struct {
   uint32_t jobs;

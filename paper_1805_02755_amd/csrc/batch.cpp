@@ -107,6 +107,7 @@ struct ce_batch {
       memset(&J, 0, sizeof J);
       J.p = params[j];
       J.tiles_x = (uint32_t)ceil_div(J.p.w, TC);
+      J.tiles_x_reciprocal = Divisor(J.tiles_x).reciprocal;
       J.tile_base = base;
       J.out = outs[j];
       base += ceil_div(J.p.h, TR) * J.tiles_x;
@@ -132,7 +133,8 @@ struct ce_batch {
       return fail(CE_E_DEVICE, "occupancy: %s", hipGetErrorString(he));
     const uint64_t packages = ceil_div(total_tiles, pkg_tiles);
     grid = (uint32_t)std::min<uint64_t>((uint64_t)std::max(1, bpc) * (uint64_t)cus, packages);
-    BatchArgs a{jobs_dev, (uint32_t)table.size(), pkg_tiles, total_tiles, counter};
+    BatchArgs a{jobs_dev, (uint32_t)table.size(), pkg_tiles, total_tiles,
+                Deal(packages, grid, pkg_tiles * (kBlockThreads / 64), counter)};
     drop_graph();
     if ((he = hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal)) != hipSuccess)
       return fail(CE_E_DEVICE, "capture: %s", hipGetErrorString(he));

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/coexec.h"
+#include "dealing.hpp"
 
 namespace ce {
 
@@ -15,15 +16,16 @@ struct alignas(64) BatchJob {
   uint32_t tiles_x;     // column blocks of this job
   uint64_t tile_base;   // first tile of this job in the concatenated space
   uint32_t* out;        // device output, h x w uint32
-  uint64_t pad[2];
+  uint32_t tiles_x_reciprocal;
+  uint32_t pad[3];
 };
 
 struct BatchArgs {
   const BatchJob* jobs;   // device table
   uint32_t n_jobs;
-  uint32_t pkg_tiles;     // tiles claimed per workgroup request
+  uint32_t pkg_tiles;     // consecutive tiles of a package
   uint64_t total_tiles;
-  uint64_t* counter;      // HBM: [0] next tile, [1] workgroups that left
+  Deal deal;              // of the packages
 };
 
 // Tile shapes the autotuner chooses from (rows x columns, 256 pixels each).

@@ -18,6 +18,7 @@
 #include "common.hpp"
 #include "device_payloads.hpp"
 #include "device_atomics.hpp"
+#include "device_divide.hpp"
 #include "device_tiles.hpp"
 #include "kernels.hpp"
 #include "rt_tile.hpp"
@@ -43,24 +44,6 @@ __global__ void k_calibrate(L1State* l1, uint32_t rounds, uint64_t spin_limit) {
 // every T-th of the package's blocks (as EscapeTile spreads a tile's), and its
 // waves take them one at a time from a counter in LDS, so that no wave waits
 // for another before the workgroup's end.
-// Division of 32-bit numbers by one the host knows: the estimate from the
-// reciprocal rounded down is at most two too small.
-struct Divisor {
-  uint32_t d, reciprocal;
-  __host__ explicit Divisor(uint32_t v) : d(v), reciprocal(0xFFFFFFFFu / v) {}
-  __device__ __forceinline__ uint32_t split(uint32_t x, uint32_t* rest) const {
-    uint32_t q = __umulhi(x, reciprocal), r = x - q * d;
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-      if (r >= d) {
-        r -= d;
-        ++q;
-      }
-    *rest = r;
-    return q;
-  }
-};
-
 constexpr uint32_t kResidentSweeps = 2048;  // eight workgroups on each of 256 compute units
 
 struct SweepArgs {
