@@ -34,7 +34,7 @@ struct ce_batch {
   bool dirty = true;       // job table or configuration changed since the graph was built
   BatchJob* jobs_dev = nullptr;
   size_t jobs_cap = 0;
-  uint64_t* counter = nullptr;
+  uint64_t* counters = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -75,9 +75,9 @@ struct ce_batch {
     }
     // cleared before anything runs on the (non-blocking) stream, which does
     // not wait for the null stream's memset
-    if ((he = hipMalloc((void**)&counter, 2 * sizeof(uint64_t))) != hipSuccess ||
-        (he = hipMemset(counter, 0, 2 * sizeof(uint64_t))) != hipSuccess || (he = hipDeviceSynchronize()) != hipSuccess)
-      return fail(CE_E_DEVICE, "counter: %s", hipGetErrorString(he));
+    if ((he = hipMalloc((void**)&counters, kDealCounterBytes)) != hipSuccess ||
+        (he = hipMemset(counters, 0, kDealCounterBytes)) != hipSuccess || (he = hipDeviceSynchronize()) != hipSuccess)
+      return fail(CE_E_DEVICE, "counters: %s", hipGetErrorString(he));
     if ((he = hipEventCreate(&ev0)) != hipSuccess || (he = hipEventCreate(&ev1)) != hipSuccess)
       return fail(CE_E_DEVICE, "events: %s", hipGetErrorString(he));
     return CE_OK;
@@ -89,7 +89,7 @@ struct ce_batch {
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
     if (jobs_dev) (void)hipFree(jobs_dev);
-    if (counter) (void)hipFree(counter);
+    if (counters) (void)hipFree(counters);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
   }
 
@@ -134,7 +134,7 @@ struct ce_batch {
     const uint64_t packages = ceil_div(total_tiles, pkg_tiles);
     grid = (uint32_t)std::min<uint64_t>((uint64_t)std::max(1, bpc) * (uint64_t)cus, packages);
     BatchArgs a{jobs_dev, (uint32_t)table.size(), pkg_tiles, total_tiles,
-                Deal(packages, grid, pkg_tiles * (kBlockThreads / 64), counter)};
+                Deal(packages, grid, pkg_tiles * (kBlockThreads / 64), counters)};
     drop_graph();
     if ((he = hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal)) != hipSuccess)
       return fail(CE_E_DEVICE, "capture: %s", hipGetErrorString(he));

@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_batch_escape(BatchArgs a) {
   extern __shared__ uint64_t sh_base[];  // first tile of each job (n_jobs entries)
   __shared__ DealState deal;
   for (uint32_t j = threadIdx.x; j < a.n_jobs; j += kBlockThreads) sh_base[j] = a.jobs[j].tile_base;
-  deal_begin(deal);
+  deal_begin(a.deal, deal);
   const uint32_t lane = threadIdx.x & 63u;
   uint32_t job = 0, part;  // job of this wave's tile, and often of its next
   uint64_t package;

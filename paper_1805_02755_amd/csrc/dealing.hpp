@@ -10,9 +10,16 @@
 // claim are T apart, rotated from one to the next, so that they do not all come
 // from one place.
 //
+// There are four counters, each with every fourth workgroup and every fourth
+// piece: one counter still bounded small batches (16 jobs of 9 million pixels,
+// packages of one and two tiles: 294 and 306 us, with 4 counters 221 and 238, 2
+// jobs of 2 million 160 and 178, now 128 and 145), while with 16 or 32 the work
+// of the banks differs by more than that gains (1,024 jobs: 9.40 ms with one
+// counter, 9.43 with 4, 9.57 and 9.91).
+//
 // The batch of 256 escape-time jobs (157 million pixels, tiles of 16 x 16) with
 // packages of 1, 2, 4 and 8 tiles taken from the counter one by one, a barrier
-// after each: 7.55, 3.91, 2.68 and 2.73 ms; dealt, 2.80, 2.60, 2.52 and 2.65. With a half of what is
+// after each: 7.55, 3.91, 2.68 and 2.73 ms; dealt, 2.68, 2.52, 2.54 and 2.64. With a half of what is
 // left in each level 3.05, 2.92, 3.03, 3.04, with a quarter 2.89, 2.71, 2.65,
 // 2.71 (a workgroup's first claim may hold far more than its share of the work);
 // with claims of fixed size and no counter 3.35, 3.43, 3.53, 3.90.
@@ -26,32 +33,37 @@
 namespace ce {
 
 constexpr uint32_t kDealLevels = 64;
-constexpr uint32_t kDealLeastParts = 8;  // of a claim, two per wave: fewer, and the counter bounds the run
+constexpr uint32_t kDealLeastParts = 8;  // of a claim, two per wave
+constexpr uint32_t kDealBanks = 4;
+constexpr uint32_t kDealBankWords = 16;  // a counter's own 128 bytes
+constexpr size_t kDealCounterBytes = (size_t)kDealBanks * kDealBankWords * sizeof(uint64_t);
 
 struct Deal {
-  Divisor groups;               // T
+  uint64_t pieces;
+  uint32_t banks;
+  Divisor groups;               // workgroups of a bank
   Divisor parts;                // waves' parts of a piece
   uint32_t turn;                // pieces the assignment is rotated by
   uint32_t levels;
-  uint64_t pieces;
-  uint64_t start[kDealLevels];  // first piece of a level
+  uint64_t start[kDealLevels];  // first of a bank's pieces in a level
   uint32_t size[kDealLevels];   // pieces of one of its claims
-  uint64_t* counter;            // HBM: [0] claims taken after level 0, [1] workgroups that left; both 0
+  uint64_t* counters;           // kDealCounterBytes, zero: a bank's claims after level 0, and its workgroups that left
 
   __host__ Deal(uint64_t n, uint32_t workgroups, uint32_t parts_per_piece, uint64_t* c)
-      : groups(workgroups), parts(parts_per_piece), turn((uint32_t)(workgroups * 5ull / 8) | 1u), levels(0), pieces(n),
-        counter(c) {
-    const uint32_t least = (uint32_t)((kDealLeastParts + parts_per_piece - 1) / parts_per_piece);
-    // an eighth, or as little more as the table has room for (n / T beyond 2^14)
+      : pieces(n), banks(workgroups % kDealBanks ? 1u : kDealBanks), groups(workgroups / banks), parts(parts_per_piece),
+        turn((uint32_t)(groups.d * 5ull / 8) | 1u), levels(0), counters(c) {
+    const uint32_t least = (kDealLeastParts + parts_per_piece - 1) / parts_per_piece;
+    const uint64_t all = n / banks + (n % banks != 0);
+    // an eighth, or as little more as the table has room for (2^14 pieces per workgroup)
     for (uint64_t share = 8; share >= 1; --share) {
       uint64_t at = 0;
-      for (levels = 0; at < n && levels < kDealLevels; ++levels) {
-        const uint64_t part = (n - at) / (share * workgroups) + (share == 1);
+      for (levels = 0; at < all && levels < kDealLevels; ++levels) {
+        const uint64_t part = (all - at) / (share * groups.d) + (share == 1);
         start[levels] = at;
         size[levels] = (uint32_t)(part > least ? part : least);
-        at += (uint64_t)size[levels] * workgroups;
+        at += (uint64_t)size[levels] * groups.d;
       }
-      if (at >= n) break;
+      if (at >= all) break;
     }
   }
 };
@@ -63,8 +75,12 @@ struct DealState {
   unsigned long long claim_part;
 };
 
-__device__ __forceinline__ void deal_begin(DealState& s) {
-  if (threadIdx.x == 0) s.claim_part = (unsigned long long)blockIdx.x << 32;
+__device__ __forceinline__ uint64_t* deal_counter(const Deal& d) {
+  return d.counters + (blockIdx.x & (d.banks - 1)) * kDealBankWords;
+}
+
+__device__ __forceinline__ void deal_begin(const Deal& d, DealState& s) {
+  if (threadIdx.x == 0) s.claim_part = (unsigned long long)(blockIdx.x / d.banks) << 32;
   __syncthreads();
 }
 
@@ -76,13 +92,14 @@ __device__ __forceinline__ bool deal_next(const Deal& d, DealState& s, uint64_t*
     unsigned long long got = 0;
     if (first) got = __hip_atomic_fetch_add(&s.claim_part, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     const uint32_t claim = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
-    uint32_t i = __builtin_amdgcn_readfirstlane((uint32_t)got), place, rotated;
+    const uint32_t i = __builtin_amdgcn_readfirstlane((uint32_t)got);
+    uint32_t place, rotated;
     const uint32_t level = d.groups.split(claim, &place);
     if (level >= d.levels) return false;
     const uint32_t all = d.size[level] * d.parts.d;
     if (i == all) {  // this wave takes the next claim for the workgroup, and waits for nobody
       if (first) {
-        const uint64_t c = d.groups.d + __hip_atomic_fetch_add(&d.counter[0], (uint64_t)1, __ATOMIC_RELAXED,
+        const uint64_t c = d.groups.d + __hip_atomic_fetch_add(deal_counter(d), (uint64_t)1, __ATOMIC_RELAXED,
                                                                __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&s.claim_part, (unsigned long long)c << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
@@ -95,20 +112,22 @@ __device__ __forceinline__ bool deal_next(const Deal& d, DealState& s, uint64_t*
     const uint32_t j = d.parts.split(i, part);
     d.groups.split(j * d.turn, &rotated);
     place += rotated;
-    *piece = d.start[level] + (uint64_t)j * d.groups.d + (place < d.groups.d ? place : place - d.groups.d);
+    const uint64_t own = d.start[level] + (uint64_t)j * d.groups.d + (place < d.groups.d ? place : place - d.groups.d);
+    *piece = own * d.banks + (blockIdx.x & (d.banks - 1));
     if (*piece < d.pieces) return true;
   }
 }
 
-// The last workgroup out re-arms the counter for the next launch (no memset
-// node is needed when the launch is replayed from a graph).
+// The last workgroup of a bank re-arms its counter for the next launch (no
+// memset node is needed when the launch is replayed from a graph).
 __device__ __forceinline__ void deal_end(const Deal& d) {
   __syncthreads();
   if (threadIdx.x != 0) return;
-  const uint64_t out = __hip_atomic_fetch_add(&d.counter[1], (uint64_t)1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  uint64_t* const c = deal_counter(d);
+  const uint64_t out = __hip_atomic_fetch_add(&c[1], (uint64_t)1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
   if (out + 1 == d.groups.d) {
-    __hip_atomic_store(&d.counter[0], (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&d.counter[1], (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&c[0], (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&c[1], (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 #endif
