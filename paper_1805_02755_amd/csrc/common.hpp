@@ -195,7 +195,7 @@ struct SchedArgs {
   L2State* l2_next;
   uint64_t* pub_next;
   uint32_t pub_next_words;
-  uint32_t pad_next;
+  uint32_t waves_alone; // 1: a workgroup's waves take the parts of its tiles on their own (WaveDealer)
 };
 
 constexpr uint32_t kFastExitMaxWgs = 65536;  // entries of the host's wg_end array

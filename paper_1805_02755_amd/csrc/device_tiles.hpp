@@ -26,6 +26,7 @@ struct EscapeTile {
   // grid run in one round
   static constexpr int kMinBlocksPerCu = 8;
   static constexpr int kMaxBlocksPerCu = 8;
+  static constexpr bool kWavesAlone = true;  // a tile's parts need no barrier between them
   ce_escape_params p;
   uint32_t* out;
   __device__ void load_constants() {}
@@ -43,18 +44,24 @@ struct EscapeTile {
   // 4096: the wave's longest is 117 steps on average against 155), and tiles
   // spread over the whole package cost nearly the same.
   __device__ void run(uint64_t g0, uint64_t g1, uint32_t t) const {
-    const uint32_t tid = thread_index(), lane = tid & 63u;
+    const uint32_t parts = tile_parts(g0, g1);
+    for (uint32_t i = __builtin_amdgcn_readfirstlane(thread_index() >> 6); i < parts; i += kBlockThreads / 64)
+      run_part(g0, g1, t, i);
+  }
+  // Blocks of a tile, at most, and block i of tile t: a wave's.
+  __device__ __forceinline__ uint32_t tile_parts(uint64_t g0, uint64_t g1) const {
+    return (uint32_t)ceil_div((uint32_t)ceil_div(p.w, kEscapeBlockCols) * (uint32_t)ceil_div(g1 - g0, kEscapeBlockRows),
+                              ntiles(g0, g1));
+  }
+  __device__ __forceinline__ void run_part(uint64_t g0, uint64_t g1, uint32_t t, uint32_t i) const {
     const uint32_t per_row = (uint32_t)ceil_div(p.w, kEscapeBlockCols);
     const uint32_t blocks = per_row * (uint32_t)ceil_div(g1 - g0, kEscapeBlockRows), nt = ntiles(g0, g1);
     const uint32_t turn = per_row * 5 / 8 < nt / 8 ? (per_row * 5 / 8) | 1u : nt / 8;
-    uint32_t i = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (uint64_t base = (uint64_t)i * nt; base < blocks; base += (uint64_t)(kBlockThreads / 64) * nt) {
-      uint32_t place = t + i * turn;
-      while (place >= nt) place -= nt;
-      const uint32_t b = (uint32_t)base + place;
-      if (b < blocks) pixel(g0 + (uint64_t)(b / per_row) * kEscapeBlockRows, g1, (b % per_row) * kEscapeBlockCols, lane);
-      i += kBlockThreads / 64;
-    }
+    uint32_t place = t + i * turn;
+    while (place >= nt) place -= nt;
+    const uint32_t b = i * nt + place;
+    if (b < blocks)
+      pixel(g0 + (uint64_t)(b / per_row) * kEscapeBlockRows, g1, (b % per_row) * kEscapeBlockCols, thread_index() & 63u);
   }
   // This lane's pixel of the block at row r0, column c0 of a package ending at row g1.
   __device__ __forceinline__ void pixel(uint64_t r0, uint64_t g1, uint32_t c0, uint32_t lane) const {
@@ -97,6 +104,7 @@ struct Blur5TileT {
   // 450 against 424 us).
   static constexpr int kMinBlocksPerCu = 5;
   static constexpr int kMaxBlocksPerCu = 6;
+  static constexpr bool kWavesAlone = false;
   ce_blur5_params p;
   const float* in;
   const float* wt;
@@ -646,6 +654,7 @@ struct NbodyTile {
   // four workgroups per CU: four waves per SIMD, 128 registers each
   static constexpr int kMinBlocksPerCu = 4;
   static constexpr int kMaxBlocksPerCu = 8;
+  static constexpr bool kWavesAlone = false;
   ce_nbody_params p;
   const float4* pos;
   float4* out;
@@ -713,6 +722,7 @@ template <bool STRICT>
 struct NbodyStepTile {
   static constexpr int kMinBlocksPerCu = 4;
   static constexpr int kMaxBlocksPerCu = 8;
+  static constexpr bool kWavesAlone = false;
   ce_nbody_step_params p;
   const float4* pos;
   const float4* vel;
@@ -820,6 +830,7 @@ __device__ __forceinline__ float binomial_leaf(float S, float f, float X) {
 struct BinomialTile {
   static constexpr int kMinBlocksPerCu = 8;
   static constexpr int kMaxBlocksPerCu = 8;
+  static constexpr bool kWavesAlone = false;
   static constexpr uint32_t kGroupsPerTile = kBlockThreads / 64;
   ce_binomial_params p;
   const float4* spots;
@@ -915,6 +926,7 @@ struct BinomialTile {
 struct BinomialCallTile {
   static constexpr int kMinBlocksPerCu = 2;
   static constexpr int kMaxBlocksPerCu = 8;
+  static constexpr bool kWavesAlone = false;
   static constexpr uint32_t kGroupsPerTile = kBlockThreads / 4;
   static constexpr int kLow = 192, kHigh = 64, kStep = 16;
   ce_binomial_params p;

@@ -44,6 +44,7 @@ inline void cpu_relax() { _mm_pause(); }
 
 constexpr uint32_t kHostNbodyTile = 16;  // bodies per host tile
 constexpr int kMaxSlots = 2;
+constexpr uint64_t kDeepEscape = 6144;  // tiles per workgroup times max_iter
 // Bounds on the waits inside the GPU kernel: every kernel ends, so the host
 // can wait for it with a plain stream synchronisation.
 constexpr uint64_t kDispenserWaitSeconds = 5;
@@ -1235,7 +1236,24 @@ struct ce_engine {
       // workgroup runs one tile either way, and the round-robin needs no
       // atomic.
       const bool uneven = kernel_id == CE_KERNEL_RUNTIME && gpu_tiles(kargs, 0, G) > (uint64_t)(grid - gather_wgs);
-      gs.stride = (gather || long_tiles || uneven) ? 0u : 1u;
+      // Escape-time with a deep cap: the blocks that run to it (some tens of
+      // microseconds each) are few, and under the round-robin the workgroups
+      // that own more of them set the time of the run, as the wave that has one
+      // does for its workgroup in every package. So tickets are atomic, and the
+      // waves take blocks on their own (WaveDealer), from two tiles per
+      // workgroup on and where tiles per workgroup times max_iter is large
+      // enough to pay for both. Co-executed under HGuided, against the
+      // round-robin and a barrier per package: 8192^2 with max_iter 4096 845
+      // against 2133 us, with 256 461 against 492; 4096^2 with 1000 212 against
+      // 273; 3000^2 with 2000 423 against 498; 1920 x 1080 with 4096 208
+      // against 454; 1500^2 with 4096 151 against 251. Below: 2048^2 with 1000
+      // (4,000) 102.5 against 101.5, with 512 92 against 76; 3000 x 2001 with
+      // 512 237 against 225; 8192^2 with 100 436 against 430, with 64 428
+      // against 358.
+      const bool deep = kernel_id == CE_KERNEL_ESCAPE && per_wg >= 2 && kargs.esc.max_iter >= 256 &&
+                        per_wg * kargs.esc.max_iter >= kDeepEscape;
+      gs.waves_alone = deep ? 1u : 0u;
+      gs.stride = (gather || long_tiles || uneven || deep) ? 0u : 1u;
       // the gatherers wait for the host's packages, whose length depends on the problem
       gs.gather_wait_ticks = std::max<uint64_t>(1, (uint64_t)((double)wallclock_hz * gather_wait_s));
       if (gather) {

@@ -27,6 +27,7 @@ CE_HD uint64_t rt_tile_items(uint64_t items) {
 struct RtTile {
   static constexpr int kMinBlocksPerCu = 1;
   static constexpr int kMaxBlocksPerCu = 8;
+  static constexpr bool kWavesAlone = false;
   ce_rt_args args;  // device pointers and scalars
   uint64_t items;   // work-items of the index space
   uint64_t lws;     // work-items per granule

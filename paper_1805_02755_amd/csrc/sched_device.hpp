@@ -341,6 +341,97 @@ __device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t*
 }
 
 
+// Deals the parts of a workgroup's tiles to its waves, which then never wait for
+// the longest of the four: parts (blocks of 64 pixels) that run to the cap take
+// tens of microseconds and most others a few, and with a barrier after each grab
+// of tiles the workgroup waits for its longest block every time. (Escape-time
+// only; where it pays is the host's decision, with the figures, in the engine.)
+// `state` counts the parts taken of the current run of tiles (next_tile's). The
+// wave that finds none left asks for the next run; the others look again until
+// it is there. What a run is lies in one of two places in turn: the one after
+// the next may be written once every part's wave has read its own (`read`).
+struct WaveRun {
+  uint64_t g0, g1;
+  uint32_t ti, step, parts, p, last;  // last: it ends its package
+};
+struct WaveDealer {
+  static constexpr uint32_t kOver = 0xFFFFFFu;  // parts of the end of all runs
+  unsigned long long state;                     // run (16 bits), its parts (24), parts taken (24)
+  WaveRun run[2];
+  uint32_t read[2], parts[2];
+  __device__ __forceinline__ void begin() {
+    state = 0;  // run 0 without parts: the first wave asks
+    for (int k = 0; k < 2; ++k) read[k] = parts[k] = 0;
+  }
+  template <class T>
+  __device__ __forceinline__ bool next(const T& pay, const SchedArgs& s, Cursor& c, WaveRun* r, uint32_t* part) {
+    const bool first = (threadIdx.x & 63u) == 0;
+    for (;;) {
+      unsigned long long got = 0;
+      if (first) got = __hip_atomic_fetch_add(&state, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)got), hi = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
+      const uint32_t taken = lo & 0xFFFFFFu, all = (hi << 8 | lo >> 24) & 0xFFFFFFu, id = hi >> 16;
+      if (all == kOver) return false;
+      if (taken < all) {
+        asm volatile("" ::: "memory");
+        const WaveRun& w = run[id & 1u];
+        r->g0 = uniform(w.g0);
+        r->g1 = uniform(w.g1);
+        r->ti = __builtin_amdgcn_readfirstlane(w.ti);
+        r->step = __builtin_amdgcn_readfirstlane(w.step);
+        r->parts = __builtin_amdgcn_readfirstlane(w.parts);
+        r->p = __builtin_amdgcn_readfirstlane(w.p);
+        r->last = __builtin_amdgcn_readfirstlane(w.last);
+        asm volatile("" ::: "memory");
+        if (first) __hip_atomic_fetch_add(&read[id & 1u], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        *part = taken;
+        return true;
+      }
+      if (taken == all) {
+        if (first) ask(pay, s, c, (id + 1) & 0xFFFFu);
+        continue;
+      }
+      // another wave asks; looking does not count as taking, however long it lasts
+      uint32_t now;
+      do {
+        __builtin_amdgcn_s_sleep(8);
+        now = __builtin_amdgcn_readfirstlane(
+            (uint32_t)(__hip_atomic_load(&state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 48));
+      } while (now == id);
+    }
+  }
+  // by one lane
+  template <class T>
+  __device__ void ask(const T& pay, const SchedArgs& s, Cursor& c, uint32_t id) {
+    const uint32_t at = id & 1u;
+    uint32_t ti = 0, count = 0, step = 0, all = kOver;
+    if (next_tile(pay, s, c, &ti, &count, &step)) {
+      // every part of the run before the last has been taken, so it is read soon
+      while (__hip_atomic_load(&read[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != parts[at]) {
+      }
+      WaveRun& w = run[at];
+      w.g0 = c.g0;
+      w.g1 = c.g1;
+      w.ti = ti;
+      w.step = step;
+      w.parts = pay.tile_parts(c.g0, c.g1);
+      w.p = c.p;
+      w.last = c.cur_t + 1 == c.base + c.nt;
+      all = count * w.parts;
+      parts[at] = all;
+      read[at] = 0;
+    }
+    // LDS operations of a wave take effect in order
+    asm volatile("" ::: "memory");
+    __hip_atomic_store(&state, (unsigned long long)id << 48 | (unsigned long long)all << 24, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  static __device__ __forceinline__ uint64_t uniform(uint64_t v) {
+    return (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32 |
+           __builtin_amdgcn_readfirstlane((uint32_t)v);
+  }
+};
+
 // Counts this workgroup out: one atomic on the line of its blockIdx mod
 // kExitLines, and one more on the shared count for the last workgroup of a
 // line. True for the last workgroup of the grid.
@@ -633,44 +724,65 @@ __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_persisten
     }
     return;
   }
-  for (;;) {
-    if (wave0) {
-      if (lane0) {
-        uint32_t p = 0, ti = 0, count = 0, step = 0;
-        uint64_t g0 = 0, g1 = 0;
-        bool go;
-        if (prev_p != 0xFFFFFFFFu) tile_finished(sa, c);
-        go = next_tile(pay, sa, c, &ti, &count, &step);
-        p = c.p;
-        g0 = c.g0;
-        g1 = c.g1;
-        sh_go = go ? 1u : 0u;
-        sh_p = p;
-        sh_ti = ti;
-        sh_count = count;
-        sh_step = step;
-        sh_g0 = g0;
-        sh_g1 = g1;
+  // Waves on their own: tiles without barriers whose cost varies.
+  bool alone = false;
+  if constexpr (T::kWavesAlone) {
+    alone = __builtin_amdgcn_readfirstlane(sa.waves_alone) != 0;
+    if (alone) {
+      __shared__ WaveDealer dealer;
+      if (threadIdx.x == 0) dealer.begin();
+      __syncthreads();
+      uint32_t part;
+      WaveRun r;
+      while (dealer.next(pay, sa, c, &r, &part)) {
+        __builtin_amdgcn_s_waitcnt(0);  // as below
+        const uint32_t k = part / r.parts;
+        pay.run_part(r.g0, r.g1, r.ti + k * r.step, part - k * r.parts);
+        if (r.last != 0 && (threadIdx.x & 63u) == 0) dev_store(&sa.pkgs[r.p].t_end, now_tick());
       }
+      __syncthreads();
     }
-    __syncthreads();
-    const uint32_t go = __builtin_amdgcn_readfirstlane(sh_go);
-    if (go == 0) break;
-    const uint32_t p = __builtin_amdgcn_readfirstlane(sh_p);
-    const uint32_t ti = __builtin_amdgcn_readfirstlane(sh_ti);
-    const uint32_t count = __builtin_amdgcn_readfirstlane(sh_count), step = __builtin_amdgcn_readfirstlane(sh_step);
-    const uint64_t g0 = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sh_g0 >> 32)) << 32) |
-                        __builtin_amdgcn_readfirstlane((uint32_t)sh_g0);
-    const uint64_t g1 = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sh_g1 >> 32)) << 32) |
-                        __builtin_amdgcn_readfirstlane((uint32_t)sh_g1);
-    // Nothing of the scheduler's may still be in flight when the payload
-    // starts: its pointers come from LDS, so its accesses are flat ones,
-    // which count against the LDS counter too; with one pending, every LDS
-    // wait inside the payload would have to drain all of them.
-    __builtin_amdgcn_s_waitcnt(0);
-    for (uint32_t k = 0; k < count; ++k) pay.run(g0, g1, ti + k * step);
-    prev_p = p;
-    __syncthreads();  // the tiles are complete and the shared slots may be reused
+  }
+  if (!alone) {
+    for (;;) {
+      if (wave0) {
+        if (lane0) {
+          uint32_t p = 0, ti = 0, count = 0, step = 0;
+          uint64_t g0 = 0, g1 = 0;
+          bool go;
+          if (prev_p != 0xFFFFFFFFu) tile_finished(sa, c);
+          go = next_tile(pay, sa, c, &ti, &count, &step);
+          p = c.p;
+          g0 = c.g0;
+          g1 = c.g1;
+          sh_go = go ? 1u : 0u;
+          sh_p = p;
+          sh_ti = ti;
+          sh_count = count;
+          sh_step = step;
+          sh_g0 = g0;
+          sh_g1 = g1;
+        }
+      }
+      __syncthreads();
+      const uint32_t go = __builtin_amdgcn_readfirstlane(sh_go);
+      if (go == 0) break;
+      const uint32_t p = __builtin_amdgcn_readfirstlane(sh_p);
+      const uint32_t ti = __builtin_amdgcn_readfirstlane(sh_ti);
+      const uint32_t count = __builtin_amdgcn_readfirstlane(sh_count), step = __builtin_amdgcn_readfirstlane(sh_step);
+      const uint64_t g0 = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sh_g0 >> 32)) << 32) |
+                          __builtin_amdgcn_readfirstlane((uint32_t)sh_g0);
+      const uint64_t g1 = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sh_g1 >> 32)) << 32) |
+                          __builtin_amdgcn_readfirstlane((uint32_t)sh_g1);
+      // Nothing of the scheduler's may still be in flight when the payload
+      // starts: its pointers come from LDS, so its accesses are flat ones,
+      // which count against the LDS counter too; with one pending, every LDS
+      // wait inside the payload would have to drain all of them.
+      __builtin_amdgcn_s_waitcnt(0);
+      for (uint32_t k = 0; k < count; ++k) pay.run(g0, g1, ti + k * step);
+      prev_p = p;
+      __syncthreads();  // the tiles are complete and the shared slots may be reused
+    }
   }
   if (wave0) {
     if (lane0) {

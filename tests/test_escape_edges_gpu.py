@@ -98,3 +98,31 @@ def test_every_pixel_once_however_the_blocks_are_dealt(w, h):
                 eng.program_out(0, dev=out, nbytes=w * h * 4)
                 eng.run()
                 assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), (workgroups, sched)
+
+
+@pytest.mark.parametrize("workgroups,max_iter", [(3, 256), (64, 600), (64, 5000), (200, 2000), (0, 300)])
+@pytest.mark.parametrize("host", [False, True])
+def test_deep_caps_in_packages(host, workgroups, max_iter):
+    """Waves that take the blocks of their workgroup's tiles on their own, over
+    many packages, with and without the host; repeated runs of one engine."""
+    w, h = 700, 501
+    x0, y0, dx, dy = (float(np.float32(v)) for v in (-2.0, -1.5, 3.0 / w, 3.0 / h))
+    prm = ce.ce_escape_params(w, h, x0, y0, dx, dy, max_iter)
+    ref = O.escape(w, h, x0, y0, dx, dy, max_iter)
+    out = torch.empty((h, w), dtype=torch.int32, device="cuda:0")
+    with ce.Engine() as eng:
+        eng.use(ce.CE_DEV_GPU | (ce.CE_DEV_HOST if host else 0), 0, 4 if host else 0)
+        eng.gpu_workgroups(workgroups)
+        eng.work_items([w, h])
+        power = [4096, 64] if host else [1]
+        for sched in (dict(kind=ce.CE_SCHED_HGUIDED, k=2, power=power, min_granules=[1] * len(power)),
+                      dict(kind=ce.CE_SCHED_DYNAMIC, package_granules=5),
+                      dict(kind=ce.CE_SCHED_DYNAMIC, package_granules=64)):
+            eng.scheduler(**sched)
+            eng.program_kernel(ce.CE_KERNEL_ESCAPE, prm)
+            eng.program_out(0, dev=out, nbytes=w * h * 4)
+            for run in range(3):
+                out.fill_(-1)
+                torch.cuda.synchronize()
+                eng.run()
+                assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), (sched, run)
