@@ -1218,10 +1218,10 @@ struct ce_engine {
       // round-robin needs no atomics, and a workgroup runs its tiles of a
       // package one after another, its waves not waiting for each other in
       // between (next_tile). Escape-time co-executed under HGuided, against
-      // atomic tickets: 2048^2 with max_iter 256 62 against 92 us, 1920 x
-      // 1080 with 1000 171 against 205, 3000^2 with 2000 0.62 against
-      // 0.84 ms, 4096^2 with 256 206 against 185 and, with the host slower,
-      // 172 against 183. With gatherers sharing some CUs the fixed
+      // atomic tickets and a barrier per tile: 2048^2 with max_iter 256 62
+      // against 92 us, 1920 x 1080 with 1000 171 against 205, 4096^2 with 256
+      // 206 against 185 and, with the host slower, 172 against 183 (deep caps:
+      // below). With gatherers sharing some CUs the fixed
       // round-robin would leave the workgroups on those CUs behind, so tiles
       // are dealt dynamically then.
       // A binomial tile runs for tens of microseconds, so one atomic per tile
