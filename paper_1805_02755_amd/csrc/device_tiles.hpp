@@ -642,10 +642,21 @@ __host__ __device__ inline uint32_t nbody_tiles(uint32_t n, uint64_t g0, uint64_
   const uint64_t end = g1 * kNbodyGranule < n ? g1 * kNbodyGranule : n;
   return g0 * kNbodyGranule < end ? (uint32_t)ceil_div(end - g0 * kNbodyGranule, group) : 0;
 }
+// The form of the engine's tiles, from the bodies alone (a share or package of
+// the space has its tiles in the form of the whole): what counts tiles, runs
+// them or picks a kernel for them asks here.
+enum class NbodyForm { kFed, kGroups, kWhole };
+template <bool STRICT>
+__host__ __device__ inline NbodyForm nbody_form(uint32_t n) {
+  return n <= kNbodyFeedMax ? NbodyForm::kFed : nbody_whole<STRICT>(n) ? NbodyForm::kWhole : NbodyForm::kGroups;
+}
 template <bool STRICT>
 __host__ __device__ inline uint32_t nbody_engine_tiles(uint32_t n, uint64_t g0, uint64_t g1) {
-  return nbody_whole<STRICT>(n) ? (uint32_t)(g1 - g0)
-                                : nbody_tiles(n, g0, g1, n <= kNbodyFeedMax ? kNbodyFeedGroup : kNbodyGroup);
+  switch (nbody_form<STRICT>(n)) {
+    case NbodyForm::kFed: return nbody_tiles(n, g0, g1, kNbodyFeedGroup);
+    case NbodyForm::kWhole: return (uint32_t)(g1 - g0);
+    default: return nbody_tiles(n, g0, g1);
+  }
 }
 
 // Accelerations: a granule is 256 bodies, a tile 64 of them or all.
@@ -663,10 +674,12 @@ struct NbodyTile {
   __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
     return nbody_engine_tiles<STRICT>(p.n, g0, g1);
   }
+  __host__ __device__ NbodyForm form() const { return nbody_form<STRICT>(p.n); }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    if (p.n <= kNbodyFeedMax)
+    const NbodyForm f = form();
+    if (f == NbodyForm::kFed)
       run_feed<kBlockThreads / 64, kNbodyFeedChunk, kNbodyLds>(g0, t);
-    else if (nbody_whole<STRICT>(p.n))
+    else if (f == NbodyForm::kWhole)
       run_whole<kNbodyLds>(g0, t);
     else
       run_group<kBlockThreads / 64, kNbodyChunk, kNbodyLds>(g0, t);
@@ -733,10 +746,12 @@ struct NbodyStepTile {
   __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
     return nbody_engine_tiles<STRICT>(p.n, g0, g1);
   }
+  __host__ __device__ NbodyForm form() const { return nbody_form<STRICT>(p.n); }
   __device__ void run(uint64_t g0, uint64_t, uint32_t t) const {
-    if (p.n <= kNbodyFeedMax)
+    const NbodyForm f = form();
+    if (f == NbodyForm::kFed)
       run_feed<kBlockThreads / 64, kNbodyFeedChunk, kNbodyLds>(g0, t);
-    else if (nbody_whole<STRICT>(p.n))
+    else if (f == NbodyForm::kWhole)
       run_whole<kNbodyLds>(g0, t);
     else
       run_group<kBlockThreads / 64, kNbodyChunk, kNbodyLds>(g0, t);

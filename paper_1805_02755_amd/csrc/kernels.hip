@@ -145,11 +145,17 @@ uint32_t sweep_workgroups(uint32_t planned, uint64_t blocks) {
   const uint32_t most = kResidentSweeps * (blocks >= 131072 ? 4u : blocks >= 65536 ? 2u : 1u);
   return planned < most ? planned : most;
 }
+// k_wide takes tiles of 64 bodies only: a small share of a space of whole
+// granules has few tiles too.
+template <class T>
+bool nbody_wide(const T& pay, uint32_t tiles) {
+  return pay.form() == NbodyForm::kGroups && tiles <= kWideMaxTiles;
+}
 template <class T>
 void launch_nbody_direct(const T& pay, const DirectArgs& d, uint32_t grid, hipStream_t st) {
-  if (pay.p.n <= kNbodyFeedMax)
+  if (pay.form() == NbodyForm::kFed)
     hipLaunchKernelGGL(k_feed<T>, dim3(grid), dim3(kFeedThreads), 0, st, pay, d);
-  else if (d.ntiles <= kWideMaxTiles)
+  else if (nbody_wide(pay, d.ntiles))
     hipLaunchKernelGGL(k_wide<T>, dim3(grid), dim3(kWideThreads), 0, st, pay, d);
   else
     hipLaunchKernelGGL(k_direct<T>, dim3(grid), dim3(kBlockThreads), 0, st, pay, d);
@@ -159,9 +165,9 @@ void launch_nbody_bare(const T& pay, uint64_t G, uint32_t tiles, hipStream_t st)
   DirectArgs d{};
   d.g1 = G;
   d.ntiles = tiles;
-  if (pay.p.n <= kNbodyFeedMax) {
+  if (pay.form() == NbodyForm::kFed) {
     hipLaunchKernelGGL(k_feed<T>, dim3(tiles), dim3(kFeedThreads), 0, st, pay, d);
-  } else if (tiles <= kWideMaxTiles) {
+  } else if (nbody_wide(pay, tiles)) {
     hipLaunchKernelGGL(k_wide<T>, dim3(tiles), dim3(kWideThreads), 0, st, pay, d);
   } else {
     hipLaunchKernelGGL(k_bare<T>, dim3(tiles), dim3(kBlockThreads), 0, st, pay, G);

@@ -100,3 +100,67 @@ def test_borders_between_forms_sampled(eng, n):
         assert not np.isnan(out).any(), (name, n)
         for i in at:
             assert same(out[i], ref[i]), (name, n, i)
+
+
+SHARES = [dict(props=[0.125]), dict(props=[0.5]), dict(props=[0.6]), dict(props=[0.75]),
+          dict(props=[0.125], n_packages=8)]
+
+
+def bound_f64(pos, i):
+    """64-bit acceleration of body i and 1e-5 of the sum of its terms' lengths."""
+    d = pos[:, :3].astype(np.float64) - pos[i, :3]
+    r2 = (d * d).sum(-1) + np.float64(np.float32(EPS2))
+    return O.nbody_acc_f64(pos, EPS2, i, i + 1)[0, :3], 1e-5 * (pos[:, 3] * np.sqrt((d * d).sum(-1)) * r2 ** -1.5).sum()
+
+
+@pytest.mark.parametrize("kind", ["acc", "step"])
+@pytest.mark.parametrize("strict", [1, 0])
+@pytest.mark.parametrize("n", [98304, 98305, 114688, 114689, 120000, 131072, 131073])
+def test_static_share_of_the_gpu_around_whole_granules(eng, n, strict, kind):
+    """The GPU's share in one package of a space beside the host: the form of the
+    tiles follows from the bodies, the kernel from the share's tiles too. Every
+    body is written, sampled ones over the share are right."""
+    pos, vel = synth.nbody_bodies(n, seed=n), synth.nbody_velocities(n, seed=n)
+    p_d, v_d = torch.from_numpy(pos).to(DEV), torch.from_numpy(vel).to(DEV)
+    dt = 0.002
+    outs = [torch.empty((n, 4), device=DEV) for _ in range(1 if kind == "acc" else 2)]
+    eng.use(ce.CE_DEV_GPU | ce.CE_DEV_HOST, 0, 0)
+    eng.work_items([n], [256])
+    if kind == "acc":
+        eng.program_kernel(ce.CE_KERNEL_NBODY_ACC, ce.ce_nbody_params(n, EPS2, strict))
+    else:
+        eng.program_kernel(ce.CE_KERNEL_NBODY_STEP, ce.ce_nbody_step_params(n, EPS2, dt, strict))
+        eng.program_in(1, host=vel, dev=v_d, nbytes=n * 16)
+    eng.program_in(0, host=pos, dev=p_d, nbytes=n * 16)
+    for s, o in enumerate(outs):
+        eng.program_out(s, dev=o, nbytes=n * 16)
+    at = sorted(set(range(0, n, n // 24)) | {n - 1})
+    if strict:
+        ref = {i: ([O.nbody_acc_body(pos, EPS2, i, True)] if kind == "acc" else
+                   O.nbody_step_body(pos, vel, EPS2, dt, i, True)) for i in at}
+    else:
+        ref = {i: bound_f64(pos, i) for i in at}
+    for share in SHARES:
+        for o in outs:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        eng.scheduler(kind=ce.CE_SCHED_STATIC, order=ce.CE_ORDER_GPU_FIRST, **share)
+        eng.run()
+        got = [o.cpu().numpy() for o in outs]
+        for g in got:
+            assert not np.isnan(g).any(), (share, int(np.isnan(g).any(1).sum()))
+        for i in at:
+            if strict:
+                assert all(same(g[i], r) for g, r in zip(got, ref[i])), (share, i)
+                continue
+            a, bound = ref[i]
+            if kind == "acc":
+                assert np.linalg.norm(got[0][i, :3] - a) <= bound, (share, i)
+                continue
+            x, v = pos[i, :3].astype(np.float64), vel[i, :3].astype(np.float64)
+            h = dt * dt / 2
+            # four roundings at most of sums and products no larger than these
+            slack = 2.0 ** -22 * (np.abs(x) + np.abs(v * dt) + np.abs(a * h) + bound * h)
+            assert np.all(np.abs(got[0][i, :3] - (x + v * dt + a * h)) <= bound * h + slack), (share, i)
+            slack = 2.0 ** -22 * (np.abs(v) + np.abs(a * dt) + bound * dt)
+            assert np.all(np.abs(got[1][i, :3] - (v + a * dt)) <= bound * dt + slack), (share, i)
