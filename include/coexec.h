@@ -168,9 +168,7 @@ typedef struct {
   double balance;                     /* min_d t_device / max_d t_device (section 7.3) */
   uint64_t total_granules;
   uint64_t total_items;
-  uint32_t gpu_workgroups;            /* grid planned for the GPU kernel of the last run (an
-                                       * escape-time run on the GPU alone, one per 512 pixels,
-                                       * folds it into at most 8192)                  */
+  uint32_t gpu_workgroups;            /* persistent grid size of the last run */
   uint32_t host_threads;              /* host worker threads of the last run  */
   double t_gather;                    /* end of the GPU's last copy of host output into
                                        * the device output (0: no such copies)  */
@@ -338,11 +336,11 @@ ce_status ce_engine_wait_bounds(ce_engine* e, double dispenser_s, double gather_
  * ceil(T / g) * ceil(g / C), the tiles run by the busiest compute unit
  * (whole rounds, spread evenly over the CUs); except that a run whose GPU
  * share is one package (the direct kernel) of equal-cost tiles with at
- * least 4 R tiles, or of runtime-payload tiles with more than 4 R, and at
- * most 65536 tiles, gets one workgroup per tile, dealt by the hardware as a
- * plain launch is (runtime tiles swizzled over the XCDs), and one of
- * escape-time plans one per tile, up to 65536, and folds them into at most
- * 8192 that share the package's pixels out between them.
+ * least 4 R tiles, or of escape-time or runtime-payload tiles with more
+ * than 4 R, and at most 65536 tiles, gets one workgroup per tile, dealt by
+ * the hardware as a plain launch is (runtime tiles swizzled over the XCDs; of
+ * escape-time the first 2 R or 4 R share the pixels out and the rest leave at
+ * once), and one of escape-time otherwise R, 2 R or 4 R, T at most.
  * A caller's value is used as
  * given (it may exceed what fits on the GPU at once: the dispenser's
  * waits do not depend on every workgroup being resident), plus the gather

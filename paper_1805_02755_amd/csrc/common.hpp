@@ -207,6 +207,7 @@ struct DirectArgs {
   uint64_t g0, g1;      // the package
   uint32_t ntiles;      // its tiles
   uint32_t swizzle;     // 1: one workgroup per tile, dealt over the XCDs in turn (see k_direct)
+  uint32_t sweepers;    // escape-time: workgroups that take part, the first ones (k_sweep_escape)
   L1State* l1;          // device address of the dispenser: the first workgroup stamps the GPU's start
   PkgSlot* pkgs;        // ... and the package's claim time into its trace record
   uint64_t* wg_end;     // each workgroup's end tick (host-coherent)

@@ -298,6 +298,7 @@ struct ce_engine {
   std::vector<ce_package_rec> trace;
   uint64_t gpu_pkgs_last = 0;
   uint32_t gpu_grid_last = 0;
+  uint32_t gpu_ends_last = 0;      // its workgroups that leave an end tick (the first ones)
   uint32_t grid_override = 0;  // persistent workgroups chosen by the caller (0: the engine chooses)
   bool pcie_stream = false;    // this run's kernel reads or writes pinned host memory directly
   uint64_t* wg_end = nullptr;      // host-coherent, kFastExitMaxWgs entries (light exit)
@@ -946,6 +947,19 @@ struct ce_engine {
     return (uint32_t)best;
   }
 
+  // Workgroups among which the escape-time sweep shares out T tiles of
+  // `blocks` blocks of 64 pixels, R workgroups resident: one round of them, two
+  // from 65,536 blocks on and four from 131,072, where the blocks still left to
+  // each even out what the rounds cost. Whole calls with 2048, 4096, 8192 and T,
+  // in us: 1920 x 1080, max_iter 1000 (32,400 blocks) 47.4, 48.5, -, 48.0; 100 x
+  // 30000, 256 (52,500) 46.3, 48.0, 48.8, 95.6; 2048^2, 256 (65,536) 42.8, 40.4,
+  // 50.8, 51.0; 2560 x 2001, 64 (80,160) 39.6, 44.1, 55.2, 57.9; 4096^2, 256
+  // (262,144) 102.5, 95.2, 91.1, 134.4; 8192^2, 4096 (1,048,576) 900, 808, 726,
+  // with 65,536 1035.
+  static uint32_t sweep_workers(uint64_t T, uint64_t blocks, uint64_t R) {
+    return (uint32_t)std::min(T, R * (blocks >= 131072 ? 4 : blocks >= 65536 ? 2 : 1));
+  }
+
   // Scratch layout of the allocation-free run: the queue state, then the
   // publication words, then the package table. Packages that fit:
   static uint64_t noalloc_max_pkgs() {
@@ -1297,6 +1311,7 @@ struct ce_engine {
     // GPU's first workgroup to stamp its start and re-anchors on it (the
     // host's own work then starts a few microseconds late).
     bool anchor_watch = false;
+    uint32_t sweepers = 0;
     if (use_gpu()) {
       gpu_preclaim(gs, grid - gather_wgs);
       // Without gather workgroups every workgroup leaves on its own (the
@@ -1318,11 +1333,17 @@ struct ce_engine {
                                    kernel_id == CE_KERNEL_RUNTIME &&
                                    gs.pre_nt > kDirectOneShotRounds * (uint64_t)resident_wgs &&
                                    gs.pre_nt <= kFastExitMaxWgs;
-      // Escape-time on the GPU alone has no tiles to deal: its direct kernel
-      // sweeps the package (launch_direct), folding the workgroups planned
-      // here, one per tile, into as many as it runs fastest with.
+      // Escape-time on the GPU alone: its direct kernel sweeps the package. It
+      // is launched like the runtime tiles, one workgroup per tile from more
+      // than four rounds on, of which the first few thousand share the pixels
+      // out and the rest leave at once; a caller's workgroups all take part.
       const bool sweep = light_exit && gs.pre_only && kernel_id == CE_KERNEL_ESCAPE;
-      if (sweep && !grid_override) grid = std::min<uint32_t>(gs.pre_nt, kFastExitMaxWgs);
+      if (sweep) {
+        const uint64_t blocks = ceil_div(esc.w, kEscapeBlockCols) * ceil_div(gs.pre_g1 - gs.pre_g0, kEscapeBlockRows);
+        sweepers = grid_override ? grid : sweep_workers(gs.pre_nt, blocks, resident_wgs);
+        const bool per_tile = gs.pre_nt > kDirectOneShotRounds * (uint64_t)resident_wgs && gs.pre_nt <= kFastExitMaxWgs;
+        if (!grid_override) grid = per_tile ? gs.pre_nt : sweepers;
+      }
       fast_exit = light_exit && gs.pre_only && (gs.stride || uneven_one_shot || sweep);
       // The fast path never touches its queue state, which therefore stays
       // clear for the next run: the buffers keep their roles, and nothing is
@@ -1347,6 +1368,7 @@ struct ce_engine {
         da.l1 = gs.l1;
         da.pkgs = gs.pkgs;
         da.wg_end = wg_end_dev;
+        da.sweepers = sweepers;
         // Tiles spanning several rounds of resident workgroups: one
         // workgroup per tile, dealt by the hardware as slots free up, as a
         // plain launch is. A fixed split over fewer workgroups keeps fewer
@@ -1383,6 +1405,7 @@ struct ce_engine {
       ph_gpu_seen = now_ns();
     }
     gpu_grid_last = grid;
+    gpu_ends_last = sweepers ? sweepers : grid;
     if (use_host()) {
       ensure_pool();
       pool_done.store(0, std::memory_order_relaxed);
@@ -1542,7 +1565,7 @@ struct ce_engine {
         // its queue state (read back only here, when statistics are asked for)
         const bool pre = fast_g1 > fast_g0;
         tl = 0;
-        for (uint32_t i = 0; i < gpu_grid_last; ++i) tl = std::max(tl, __atomic_load_n(&wg_end[i], __ATOMIC_ACQUIRE));
+        for (uint32_t i = 0; i < gpu_ends_last; ++i) tl = std::max(tl, __atomic_load_n(&wg_end[i], __ATOMIC_ACQUIRE));
         np = pre ? 1 : 0;
         gr = fast_g1 - fast_g0;
         if (!fast_exit) {
@@ -1597,7 +1620,7 @@ struct ce_engine {
     if (gi >= 0 && gpu_pkgs_last && fast_exit) {
       // the one pre-claimed package: its record is the host's own
       uint64_t tl = 0;
-      for (uint32_t i = 0; i < gpu_grid_last; ++i) tl = std::max(tl, __atomic_load_n(&wg_end[i], __ATOMIC_ACQUIRE));
+      for (uint32_t i = 0; i < gpu_ends_last; ++i) tl = std::max(tl, __atomic_load_n(&wg_end[i], __ATOMIC_ACQUIRE));
       const uint64_t tf = __atomic_load_n(&l1->gpu_t_first, __ATOMIC_ACQUIRE);
       trace.push_back(ce_package_rec{(uint32_t)gi, 0, fast_g0, fast_g1, tick_to_host_s(tf), tick_to_host_s(tl)});
     } else if (gi >= 0 && gpu_pkgs_last) {

@@ -43,9 +43,8 @@ __global__ void k_calibrate(L1State* l1, uint32_t rounds, uint64_t spin_limit) {
 // Escape-time over one package, the GPU alone: no tiles. Workgroup t of T owns
 // every T-th of the package's blocks (as EscapeTile spreads a tile's), and its
 // waves take them one at a time from a counter in LDS, so that no wave waits
-// for another before the workgroup's end.
-constexpr uint32_t kResidentSweeps = 2048;  // eight workgroups on each of 256 compute units
-
+// for another before the workgroup's end. T is the sweepers of the launch; a
+// workgroup beyond them has no pixels.
 struct SweepArgs {
   uint32_t blocks;  // of the package
   uint32_t turn;    // blocks the assignment is rotated by from one round of T blocks to the next, below T
@@ -56,6 +55,7 @@ struct SweepArgs {
 __global__ __launch_bounds__(kBlockThreads, EscapeTile::kMinBlocksPerCu) void k_sweep_escape(EscapeTile pay, DirectArgs d,
                                                                                             SweepArgs s) {
   __shared__ uint32_t next;
+  if (blockIdx.x >= d.sweepers) return;
   const bool first = threadIdx.x == 0;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
   if (first) {
@@ -135,16 +135,6 @@ __global__ __launch_bounds__(kFeedThreads, 4) void k_feed(T pay, DirectArgs d) {
 
 // ------------------------------------------------------------ host helpers
 namespace {
-// The sweep's workgroups: one round of resident ones, two from 65,536 blocks
-// on and four from 131,072, where the blocks still left to each even out what
-// the rounds cost; never more than the engine planned. Measured at 2048, 4096
-// and 8192: 1920 x 1080, max_iter 1000 (32,400 blocks) 49.8, 53.8, 61.0 us;
-// 2048 x 2048, 256 (65,536) 46.3, 45.1, 57.5; 4096 x 4096, 256 (262,144) 129,
-// 120, 116; 8192 x 8192, 4096 (1,048,576) 1049, 1014, 912.
-uint32_t sweep_workgroups(uint32_t planned, uint64_t blocks) {
-  const uint32_t most = kResidentSweeps * (blocks >= 131072 ? 4u : blocks >= 65536 ? 2u : 1u);
-  return planned < most ? planned : most;
-}
 // k_wide takes tiles of 64 bodies only: a small share of a space of whole
 // granules has few tiles too.
 template <class T>
@@ -289,9 +279,10 @@ hipError_t launch_direct(const KernelArgs& a, const DirectArgs& d, uint32_t grid
         hipLaunchKernelGGL(k_direct<EscapeTile>, g, b, 0, st, make_escape(a), d);
         break;
       }
-      const uint32_t T = sweep_workgroups(grid, blocks);
+      const uint32_t T = d.sweepers;
+      if (T == 0 || T > grid) return hipErrorInvalidValue;
       const SweepArgs s{(uint32_t)blocks, ((uint32_t)(per_row * 5 / 8) | 1u) % T, Divisor((uint32_t)per_row), Divisor(T)};
-      hipLaunchKernelGGL(k_sweep_escape, dim3(T), b, 0, st, make_escape(a), d, s);
+      hipLaunchKernelGGL(k_sweep_escape, g, b, 0, st, make_escape(a), d, s);
       break;
     }
     case CE_KERNEL_BLUR5: hipLaunchKernelGGL(k_direct<Blur5Tile>, g, b, 0, st, make_blur(a), d); break;
