@@ -350,6 +350,9 @@ __device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t*
 // wave that finds none left asks for the next run; the others look again until
 // it is there. What a run is lies in one of two places in turn: the one after
 // the next may be written once every part's wave has read its own (`read`).
+// `state` is stored with release and taken with acquire order, so that it hands
+// over the run's record and the cursor whatever instructions they are kept with
+// (a flat access is not ordered with the LDS instructions of its wave).
 struct WaveRun {
   uint64_t g0, g1;
   uint32_t ti, step, parts, p, last;  // last: it ends its package
@@ -368,12 +371,11 @@ struct WaveDealer {
     const bool first = (threadIdx.x & 63u) == 0;
     for (;;) {
       unsigned long long got = 0;
-      if (first) got = __hip_atomic_fetch_add(&state, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (first) got = __hip_atomic_fetch_add(&state, 1ull, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
       const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)got), hi = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
       const uint32_t taken = lo & 0xFFFFFFu, all = (hi << 8 | lo >> 24) & 0xFFFFFFu, id = hi >> 16;
       if (all == kOver) return false;
       if (taken < all) {
-        asm volatile("" ::: "memory");
         const WaveRun& w = run[id & 1u];
         r->g0 = uniform(w.g0);
         r->g1 = uniform(w.g1);
@@ -382,8 +384,7 @@ struct WaveDealer {
         r->parts = __builtin_amdgcn_readfirstlane(w.parts);
         r->p = __builtin_amdgcn_readfirstlane(w.p);
         r->last = __builtin_amdgcn_readfirstlane(w.last);
-        asm volatile("" ::: "memory");
-        if (first) __hip_atomic_fetch_add(&read[id & 1u], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (first) __hip_atomic_fetch_add(&read[id & 1u], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         *part = taken;
         return true;
       }
@@ -402,12 +403,12 @@ struct WaveDealer {
   }
   // by one lane
   template <class T>
-  __device__ void ask(const T& pay, const SchedArgs& s, Cursor& c, uint32_t id) {
+  __device__ __forceinline__ void ask(const T& pay, const SchedArgs& s, Cursor& c, uint32_t id) {
     const uint32_t at = id & 1u;
     uint32_t ti = 0, count = 0, step = 0, all = kOver;
     if (next_tile(pay, s, c, &ti, &count, &step)) {
       // every part of the run before the last has been taken, so it is read soon
-      while (__hip_atomic_load(&read[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != parts[at]) {
+      while (__hip_atomic_load(&read[at], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != parts[at]) {
       }
       WaveRun& w = run[at];
       w.g0 = c.g0;
@@ -421,9 +422,8 @@ struct WaveDealer {
       parts[at] = all;
       read[at] = 0;
     }
-    // LDS operations of a wave take effect in order
-    asm volatile("" ::: "memory");
-    __hip_atomic_store(&state, (unsigned long long)id << 48 | (unsigned long long)all << 24, __ATOMIC_RELAXED,
+    // the run's record, and the cursor, which the next wave to ask goes on with
+    __hip_atomic_store(&state, (unsigned long long)id << 48 | (unsigned long long)all << 24, __ATOMIC_RELEASE,
                        __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   static __device__ __forceinline__ uint64_t uniform(uint64_t v) {
@@ -675,8 +675,9 @@ __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_persisten
     for (uint32_t i = blockIdx.x * kBlockThreads + threadIdx.x; i < words; i += gridDim.x * kBlockThreads)
       dev_store(i < kStateWords ? &st[i] : &sa.pub_next[i - kStateWords], (uint64_t)0);
   }
-  // The cursor lives in LDS too: only lane 0 of wave 0 uses it, and keeping
-  // it in registers across the tile loop would cost the payload occupancy.
+  // The cursor lives in LDS too: one lane at a time uses it (lane 0 of wave 0,
+  // or of the wave that asks, see WaveDealer), and keeping it in registers across
+  // the tile loop would cost the payload occupancy.
   __shared__ Cursor sh_cursor;
   Cursor& c = sh_cursor;
   if (wave0) {
