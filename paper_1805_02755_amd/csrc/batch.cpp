@@ -133,8 +133,8 @@ struct ce_batch {
       return fail(CE_E_DEVICE, "occupancy: %s", hipGetErrorString(he));
     const uint64_t packages = ceil_div(total_tiles, pkg_tiles);
     grid = (uint32_t)std::min<uint64_t>((uint64_t)std::max(1, bpc) * (uint64_t)cus, packages);
-    BatchArgs a{jobs_dev, (uint32_t)table.size(), pkg_tiles, total_tiles,
-                Deal(packages, grid, pkg_tiles * (kBlockThreads / 64), counters)};
+    constexpr uint32_t kParts = kBlockThreads / 64;  // of a tile
+    BatchArgs a{jobs_dev, (uint32_t)table.size(), pkg_tiles, Deal(total_tiles * kParts, grid, pkg_tiles * kParts, counters)};
     drop_graph();
     if ((he = hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal)) != hipSuccess)
       return fail(CE_E_DEVICE, "capture: %s", hipGetErrorString(he));

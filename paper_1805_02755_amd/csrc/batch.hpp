@@ -24,7 +24,6 @@ struct BatchArgs {
   const BatchJob* jobs;   // device table
   uint32_t n_jobs;
   uint32_t pkg_tiles;     // consecutive tiles of a package
-  uint64_t total_tiles;
   Deal deal;              // of the packages
 };
 

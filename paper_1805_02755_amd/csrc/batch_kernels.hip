@@ -31,7 +31,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_batch_escape(BatchArgs a) {
   uint64_t package;
   while (deal_next(a.deal, deal, &package, &part)) {
     const uint64_t t = package * a.pkg_tiles + part / kWaves;
-    if (t >= a.total_tiles) continue;
     if (t < sh_base[job] || (job + 1 < a.n_jobs && sh_base[job + 1] <= t)) {
       uint32_t l = 0, h = a.n_jobs;  // sh_base[l] <= t < sh_base[h] (sh_base[n_jobs] = end)
       while (h - l > 1) {

@@ -39,7 +39,7 @@ constexpr uint32_t kDealBankWords = 16;  // a counter's own 128 bytes
 constexpr size_t kDealCounterBytes = (size_t)kDealBanks * kDealBankWords * sizeof(uint64_t);
 
 struct Deal {
-  uint64_t pieces;
+  uint64_t pieces, all_parts;   // the last piece may be short
   uint32_t banks;
   Divisor groups;               // workgroups of a bank
   Divisor parts;                // waves' parts of a piece
@@ -49,11 +49,11 @@ struct Deal {
   uint32_t size[kDealLevels];   // pieces of one of its claims
   uint64_t* counters;           // kDealCounterBytes, zero: a bank's claims after level 0, and its workgroups that left
 
-  __host__ Deal(uint64_t n, uint32_t workgroups, uint32_t parts_per_piece, uint64_t* c)
-      : pieces(n), banks(workgroups % kDealBanks ? 1u : kDealBanks), groups(workgroups / banks), parts(parts_per_piece),
+  __host__ Deal(uint64_t n_parts, uint32_t workgroups, uint32_t parts_per_piece, uint64_t* c)
+      : pieces(n_parts / parts_per_piece + (n_parts % parts_per_piece != 0)), all_parts(n_parts), banks(workgroups % kDealBanks ? 1u : kDealBanks), groups(workgroups / banks), parts(parts_per_piece),
         turn((uint32_t)(groups.d * 5ull / 8) | 1u), levels(0), counters(c) {
     const uint32_t least = (kDealLeastParts + parts_per_piece - 1) / parts_per_piece;
-    const uint64_t all = n / banks + (n % banks != 0);
+    const uint64_t all = pieces / banks + (pieces % banks != 0);
     // an eighth, or as little more as the table has room for (2^14 pieces per workgroup)
     for (uint64_t share = 8; share >= 1; --share) {
       uint64_t at = 0;
@@ -114,7 +114,12 @@ __device__ __forceinline__ bool deal_next(const Deal& d, DealState& s, uint64_t*
     place += rotated;
     const uint64_t own = d.start[level] + (uint64_t)j * d.groups.d + (place < d.groups.d ? place : place - d.groups.d);
     *piece = own * d.banks + (blockIdx.x & (d.banks - 1));
-    if (*piece < d.pieces) return true;
+    if (*piece + 1 < d.pieces || *piece * d.parts.d + *part < d.all_parts) return true;
+    // nothing left in this piece: on to the next (unless the claim is over), not
+    // part by part, since a caller's piece may have millions
+    if (first)
+      __hip_atomic_fetch_max(&s.claim_part, (unsigned long long)claim << 32 | (j + 1) * d.parts.d, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 
