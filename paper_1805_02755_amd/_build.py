@@ -40,6 +40,7 @@ def _run(cmd, verbose):
 # found by its bare name).
 RT_HEADERS = [("common.hpp", os.path.join(CSRC, "common.hpp")),
               ("device_atomics.hpp", os.path.join(CSRC, "device_atomics.hpp")),
+              ("device_divide.hpp", os.path.join(CSRC, "device_divide.hpp")),
               ("sched_device.hpp", os.path.join(CSRC, "sched_device.hpp")),
               ("rt_tile.hpp", os.path.join(CSRC, "rt_tile.hpp")),
               ("coexec.h", os.path.join(PKG, "..", "include", "coexec.h"))]

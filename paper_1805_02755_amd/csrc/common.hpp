@@ -18,11 +18,19 @@ enum SchedKind : uint32_t { kStatic = 0, kDynamic = 1, kHGuided = 2 };
 // 2-D payloads: a tile is kTileRows rows by one column block.
 constexpr uint32_t kEscapeTileRows = 1;
 constexpr uint32_t kEscapeTileCols = 512;
-constexpr uint32_t kEscapeBlockCols = 16, kEscapeBlockRows = 4;  // pixels of one wave
 constexpr uint32_t kBlurTileRows = 32;
 constexpr uint32_t kBlurTileCols = 1024;  // 256 threads x 4 columns
 constexpr uint32_t kNbodyGranule = 256;   // bodies per granule (1-D lws)
 constexpr uint32_t kBlockThreads = 256;
+
+// Blocks of 64 pixels, one wave's, that a package of `rows` rows is cut into:
+// 2^bits columns of 64 / 2^bits rows. 16 x 4 keeps a wave's orbits closest in
+// length, but in packages of one and two rows a wave would do the work of a block
+// for a quarter and a half of its pixels: those take blocks of 64 x 1 and 32 x 2.
+// 8192 x 4096, the GPU alone, Dynamic, in blocks of 16 x 4 and so: rows of a
+// package 1, max_iter 16, 256, 1000 1245, 1826, 1931 -> 1054, 1135, 1191 us, rows 2
+// 810, 1089, 1159 -> 719, 820, 871; one row of 16.8 million pixels, 256 302 -> 94.
+CE_HD uint32_t escape_block_bits(uint64_t rows) { return rows < 3 ? 7u - (uint32_t)rows : 4u; }
 
 // Whether the GPU prices binomial calls one per lane (tiles of 64 groups)
 // rather than one group per wave (tiles of four): `groups` is the GPU's share
@@ -228,5 +236,12 @@ CE_HD uint64_t hguided_size(uint64_t G_r, uint64_t P_i, uint64_t sumP, uint32_t 
 CE_HD uint64_t band_edge(uint64_t b, uint64_t G, uint64_t nb) { return nb ? (b * G) / nb : 0; }
 
 CE_HD uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
+
+// Blocks side by side in a row of w pixels, and one below the other (with shifts:
+// the compiler cannot tell that 64 >> bits is a power of two).
+CE_HD uint32_t escape_blocks_across(uint32_t w, uint32_t bits) {
+  return (uint32_t)(((uint64_t)w + ((1u << bits) - 1u)) >> bits);
+}
+CE_HD uint64_t escape_blocks_down(uint64_t rows, uint32_t bits) { return (rows + ((64u >> bits) - 1u)) >> (6u - bits); }
 
 }  // namespace ce

@@ -10,7 +10,7 @@ namespace ce {
 // reciprocal rounded down is at most two too small.
 struct Divisor {
   uint32_t d, reciprocal;
-  __host__ explicit Divisor(uint32_t v) : d(v), reciprocal(0xFFFFFFFFu / v) {}
+  __host__ __device__ explicit Divisor(uint32_t v) : d(v), reciprocal(0xFFFFFFFFu / v) {}
   __host__ __device__ Divisor(uint32_t v, uint32_t r) : d(v), reciprocal(r) {}
   __host__ __device__ uint32_t split(uint32_t x, uint32_t* rest) const {
     uint32_t q = (uint32_t)(((uint64_t)x * reciprocal) >> 32), r = x - q * d;

@@ -8,6 +8,7 @@
 
 #include "../../include/coexec.h"
 #include "common.hpp"
+#include "device_divide.hpp"
 #include "device_payloads.hpp"
 
 namespace ce {
@@ -29,6 +30,9 @@ struct EscapeTile {
   static constexpr bool kWavesAlone = true;  // a tile's parts need no barrier between them
   ce_escape_params p;
   uint32_t* out;
+  Divisor across;  // blocks of 16 x 4 side by side
+  __host__ __device__ EscapeTile(const ce_escape_params& params, uint32_t* o)
+      : p(params), out(o), across(escape_blocks_across(params.w, 4)) {}
   __device__ void load_constants() {}
   __host__ __device__ uint32_t ncb() const { return (uint32_t)ceil_div(p.w, kEscapeTileCols); }
   __host__ __device__ uint64_t granules() const { return p.h; }
@@ -36,37 +40,49 @@ struct EscapeTile {
     return (uint32_t)(ceil_div(g1 - g0, kEscapeTileRows) * ncb());
   }
   // A tile is as many pixels as kEscapeTileRows x kEscapeTileCols, but not a
-  // stretch of a row: the package is cut into blocks of kEscapeBlockCols x
-  // kEscapeBlockRows pixels, one wave's, and tile t of nt takes every nt-th
-  // block (the start rotated from one round of blocks to the next, so that a
-  // tile's blocks do not all lie in one column). Blocks of 16 x 4 keep a
+  // stretch of a row: the package is cut into blocks of 64 pixels (16 x 4 where
+  // its rows allow, escape_block_bits), one wave's, and tile t of nt takes every
+  // nt-th block (the start rotated from one round of blocks to the next, so that
+  // a tile's blocks do not all lie in one column). Blocks of 16 x 4 keep a
   // wave's orbits closer in length than rows of 64 (8192 x 8192, max_iter
   // 4096: the wave's longest is 117 steps on average against 155), and tiles
   // spread over the whole package cost nearly the same.
   __device__ void run(uint64_t g0, uint64_t g1, uint32_t t) const {
-    const uint32_t parts = tile_parts(g0, g1);
-    for (uint32_t i = __builtin_amdgcn_readfirstlane(thread_index() >> 6); i < parts; i += kBlockThreads / 64)
+    const uint32_t all = blocks(g0, g1), nt = ntiles(g0, g1);
+    for (uint32_t i = __builtin_amdgcn_readfirstlane(thread_index() >> 6); i * nt < all; i += kBlockThreads / 64)
       run_part(g0, g1, t, i);
+  }
+  __device__ __forceinline__ uint32_t blocks(uint64_t g0, uint64_t g1) const {
+    const uint32_t bits = escape_block_bits(g1 - g0);
+    return escape_blocks_across(p.w, bits) * (uint32_t)escape_blocks_down(g1 - g0, bits);
   }
   // Blocks of a tile, at most, and block i of tile t: a wave's.
   __device__ __forceinline__ uint32_t tile_parts(uint64_t g0, uint64_t g1) const {
-    return (uint32_t)ceil_div((uint32_t)ceil_div(p.w, kEscapeBlockCols) * (uint32_t)ceil_div(g1 - g0, kEscapeBlockRows),
-                              ntiles(g0, g1));
+    const uint32_t all = blocks(g0, g1), nt = ntiles(g0, g1);
+    return all / nt + (all % nt != 0);
   }
   __device__ __forceinline__ void run_part(uint64_t g0, uint64_t g1, uint32_t t, uint32_t i) const {
-    const uint32_t per_row = (uint32_t)ceil_div(p.w, kEscapeBlockCols);
-    const uint32_t blocks = per_row * (uint32_t)ceil_div(g1 - g0, kEscapeBlockRows), nt = ntiles(g0, g1);
+    const uint32_t bits = escape_block_bits(g1 - g0), per_row = escape_blocks_across(p.w, bits), nt = ntiles(g0, g1);
     const uint32_t turn = per_row * 5 / 8 < nt / 8 ? (per_row * 5 / 8) | 1u : nt / 8;
     uint32_t place = t + i * turn;
     while (place >= nt) place -= nt;
     const uint32_t b = i * nt + place;
-    if (b < blocks)
-      pixel(g0 + (uint64_t)(b / per_row) * kEscapeBlockRows, g1, (b % per_row) * kEscapeBlockCols, thread_index() & 63u);
+    if (b >= blocks(g0, g1)) return;
+    uint32_t bx, by;
+    if (bits == 4) {
+      by = across.split(b, &bx);
+    } else {
+      by = b / per_row;
+      bx = b - by * per_row;
+    }
+    pixel(g0, g1, __builtin_amdgcn_readfirstlane(by), __builtin_amdgcn_readfirstlane(bx), bits, thread_index() & 63u);
   }
-  // This lane's pixel of the block at row r0, column c0 of a package ending at row g1.
-  __device__ __forceinline__ void pixel(uint64_t r0, uint64_t g1, uint32_t c0, uint32_t lane) const {
-    const uint64_t r = r0 + lane / kEscapeBlockCols;
-    const uint32_t c = c0 + lane % kEscapeBlockCols;
+  // This lane's pixel of the block that is the by-th down and the bx-th across
+  // of a package of rows g0 .. g1.
+  __device__ __forceinline__ void pixel(uint64_t g0, uint64_t g1, uint32_t by, uint32_t bx, uint32_t bits,
+                                        uint32_t lane) const {
+    const uint64_t r = g0 + ((uint64_t)by << (6u - bits)) + (lane >> bits);
+    const uint32_t c = (bx << bits) + (lane & ((1u << bits) - 1u));
     if (r < g1 && c < p.w) {
       const float cr = p.x0 + (float)c * p.dx;
       const float ci = p.y0 + (float)r * p.dy;

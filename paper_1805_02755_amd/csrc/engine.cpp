@@ -1339,7 +1339,8 @@ struct ce_engine {
       // out and the rest leave at once; a caller's workgroups all take part.
       const bool sweep = light_exit && gs.pre_only && kernel_id == CE_KERNEL_ESCAPE;
       if (sweep) {
-        const uint64_t blocks = ceil_div(esc.w, kEscapeBlockCols) * ceil_div(gs.pre_g1 - gs.pre_g0, kEscapeBlockRows);
+        const uint64_t rows = gs.pre_g1 - gs.pre_g0, bits = escape_block_bits(rows);
+        const uint64_t blocks = escape_blocks_across(esc.w, bits) * escape_blocks_down(rows, bits);
         sweepers = grid_override ? grid : sweep_workers(gs.pre_nt, blocks, resident_wgs);
         const bool per_tile = gs.pre_nt > kDirectOneShotRounds * (uint64_t)resident_wgs && gs.pre_nt <= kFastExitMaxWgs;
         if (!grid_override) grid = per_tile ? gs.pre_nt : sweepers;

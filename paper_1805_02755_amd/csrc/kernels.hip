@@ -47,6 +47,7 @@ __global__ void k_calibrate(L1State* l1, uint32_t rounds, uint64_t spin_limit) {
 // workgroup beyond them has no pixels.
 struct SweepArgs {
   uint32_t blocks;  // of the package
+  uint32_t bits;    // their columns, as a power of two
   uint32_t turn;    // blocks the assignment is rotated by from one round of T blocks to the next, below T
   Divisor per_row;  // blocks side by side
   Divisor round;    // T
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(kBlockThreads, EscapeTile::kMinBlocksPerCu) void k_
     const uint32_t b = base + place;
     if (b < s.blocks) {
       const uint32_t by = s.per_row.split(b, &bx);
-      pay.pixel(d.g0 + (uint64_t)by * kEscapeBlockRows, d.g1, bx * kEscapeBlockCols, lane);
+      pay.pixel(d.g0, d.g1, by, bx, s.bits, lane);
     }
     uint32_t taken = 0;
     if (lane == 0) taken = __hip_atomic_fetch_add(&next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -163,7 +164,7 @@ void launch_nbody_bare(const T& pay, uint64_t G, uint32_t tiles, hipStream_t st)
     hipLaunchKernelGGL(k_bare<T>, dim3(tiles), dim3(kBlockThreads), 0, st, pay, G);
   }
 }
-EscapeTile make_escape(const KernelArgs& a) { return EscapeTile{a.esc, (uint32_t*)a.out}; }
+EscapeTile make_escape(const KernelArgs& a) { return EscapeTile(a.esc, (uint32_t*)a.out); }
 Blur5Tile make_blur(const KernelArgs& a) {
   return Blur5Tile{a.blur, (const float*)a.in0, (const float*)a.in1, (float*)a.out, {}};
 }
@@ -274,14 +275,15 @@ hipError_t launch_direct(const KernelArgs& a, const DirectArgs& d, uint32_t grid
   const dim3 g(grid), b(kBlockThreads);
   switch (a.kernel_id) {
     case CE_KERNEL_ESCAPE: {
-      const uint64_t per_row = ceil_div(a.esc.w, kEscapeBlockCols), blocks = per_row * ceil_div(d.g1 - d.g0, kEscapeBlockRows);
+      const uint32_t bits = escape_block_bits(d.g1 - d.g0);
+      const uint64_t per_row = escape_blocks_across(a.esc.w, bits), blocks = per_row * escape_blocks_down(d.g1 - d.g0, bits);
       if (blocks >= (1ull << 30)) {
         hipLaunchKernelGGL(k_direct<EscapeTile>, g, b, 0, st, make_escape(a), d);
         break;
       }
       const uint32_t T = d.sweepers;
       if (T == 0 || T > grid) return hipErrorInvalidValue;
-      const SweepArgs s{(uint32_t)blocks, ((uint32_t)(per_row * 5 / 8) | 1u) % T, Divisor((uint32_t)per_row), Divisor(T)};
+      const SweepArgs s{(uint32_t)blocks, bits, ((uint32_t)(per_row * 5 / 8) | 1u) % T, Divisor((uint32_t)per_row), Divisor(T)};
       hipLaunchKernelGGL(k_sweep_escape, g, b, 0, st, make_escape(a), d, s);
       break;
     }

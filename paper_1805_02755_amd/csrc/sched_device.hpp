@@ -10,6 +10,7 @@
 
 #include "common.hpp"
 #include "device_atomics.hpp"
+#include "device_divide.hpp"
 
 namespace ce {
 
@@ -355,7 +356,7 @@ __device__ bool next_tile(const T& pay, const SchedArgs& s, Cursor& c, uint32_t*
 // (a flat access is not ordered with the LDS instructions of its wave).
 struct WaveRun {
   uint64_t g0, g1;
-  uint32_t ti, step, parts, p, last;  // last: it ends its package
+  uint32_t ti, step, parts, parts_reciprocal, p, last;  // parts of a tile; last: it ends its package
 };
 struct WaveDealer {
   static constexpr uint32_t kOver = 0xFFFFFFu;  // parts of the end of all runs
@@ -382,6 +383,7 @@ struct WaveDealer {
         r->ti = __builtin_amdgcn_readfirstlane(w.ti);
         r->step = __builtin_amdgcn_readfirstlane(w.step);
         r->parts = __builtin_amdgcn_readfirstlane(w.parts);
+        r->parts_reciprocal = __builtin_amdgcn_readfirstlane(w.parts_reciprocal);
         r->p = __builtin_amdgcn_readfirstlane(w.p);
         r->last = __builtin_amdgcn_readfirstlane(w.last);
         if (first) __hip_atomic_fetch_add(&read[id & 1u], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -416,6 +418,7 @@ struct WaveDealer {
       w.ti = ti;
       w.step = step;
       w.parts = pay.tile_parts(c.g0, c.g1);
+      w.parts_reciprocal = Divisor(w.parts).reciprocal;
       w.p = c.p;
       w.last = c.cur_t + 1 == c.base + c.nt;
       all = count * w.parts;
@@ -737,8 +740,9 @@ __global__ __launch_bounds__(kBlockThreads, T::kMinBlocksPerCu) void k_persisten
       WaveRun r;
       while (dealer.next(pay, sa, c, &r, &part)) {
         __builtin_amdgcn_s_waitcnt(0);  // as below
-        const uint32_t k = part / r.parts;
-        pay.run_part(r.g0, r.g1, r.ti + k * r.step, part - k * r.parts);
+        uint32_t i;
+        const uint32_t k = Divisor(r.parts, r.parts_reciprocal).split(part, &i);
+        pay.run_part(r.g0, r.g1, __builtin_amdgcn_readfirstlane(r.ti + k * r.step), __builtin_amdgcn_readfirstlane(i));
         if (r.last != 0 && (threadIdx.x & 63u) == 0) dev_store(&sa.pkgs[r.p].t_end, now_tick());
       }
       __syncthreads();

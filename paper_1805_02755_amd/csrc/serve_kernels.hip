@@ -125,7 +125,7 @@ __device__ bool serve_next(const ServeArgs& a, uint64_t t_start, uint32_t* p_cac
 __device__ void serve_tile(const ServeDesc& d, uint32_t ti) {
   const uint32_t kind = __builtin_amdgcn_readfirstlane(d.kind);
   if (kind == CE_KERNEL_ESCAPE) {
-    EscapeTile e{d.esc, (uint32_t*)d.out};
+    EscapeTile e(d.esc, (uint32_t*)d.out);
     e.run(0, d.granules, ti);
   } else if (kind == CE_KERNEL_BLUR5) {
     Blur5TileFresh b{d.blur, (const float*)d.in0, (const float*)d.in1, (float*)d.out, {}};
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kBlockThreads, 5) void k_serve(ServeArgs a) {
 
 uint32_t serve_tiles(const ServeDesc& d) {
   switch (d.kind) {
-    case CE_KERNEL_ESCAPE: return EscapeTile{d.esc, nullptr}.ntiles(0, d.esc.h);
+    case CE_KERNEL_ESCAPE: return EscapeTile(d.esc, nullptr).ntiles(0, d.esc.h);
     case CE_KERNEL_BLUR5: return Blur5Tile{d.blur, nullptr, nullptr, nullptr, {}}.ntiles(0, d.blur.h);
     case CE_KERNEL_NBODY_ACC:
       return d.nb.n >= kServeWholeBodies ? (uint32_t)ceil_div(d.nb.n, kNbodyGranule)

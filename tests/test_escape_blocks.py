@@ -1,0 +1,43 @@
+"""How a package of escape-time rows is cut into the waves' blocks of 64 pixels
+(common.hpp, shared by the engine and its kernels): the blocks cover the package,
+and a wave's work is pixels, not padding, however few rows a package has."""
+import os
+import subprocess
+
+import pytest
+
+from test_kernel_isa import CSRC
+
+SRC = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "common.hpp"
+int main(int, char** a) {
+  const uint32_t w = (uint32_t)strtoull(a[1], 0, 0);
+  for (uint64_t rows = 1; rows <= 40; ++rows) {
+    const uint32_t bits = ce::escape_block_bits(rows);
+    printf("%llu %u %llu %llu\n", (unsigned long long)rows, bits, (unsigned long long)ce::escape_blocks_across(w, bits),
+           (unsigned long long)ce::escape_blocks_down(rows, bits));
+  }
+}
+"""
+
+
+@pytest.mark.parametrize("w", [1, 15, 16, 17, 63, 64, 65, 1000, 8192, 0xFFFFFFFF])
+def test_blocks_cover_the_package_without_padding_rows(tmp_path, w):
+    src = tmp_path / "blocks.cpp"
+    src.write_text(SRC)
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", str(tmp_path / "blocks"), str(src)], check=True)
+    out = subprocess.run([str(tmp_path / "blocks"), str(w)], check=True, capture_output=True, text=True).stdout
+    rows_seen = 0
+    for line in out.splitlines():
+        rows, bits, across, down = (int(x) for x in line.split())
+        cols, high = 1 << bits, 64 >> bits
+        assert cols * high == 64
+        assert (across - 1) * cols < w <= across * cols
+        assert (down - 1) * high < rows <= down * high
+        assert down * high * 3 <= rows * 5, (rows, high)  # of 3 and 5 rows a third and three fifths are padding
+        if rows <= 2:
+            assert down * high == rows
+        rows_seen += 1
+    assert rows_seen == 40

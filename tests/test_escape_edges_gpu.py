@@ -126,3 +126,31 @@ def test_deep_caps_in_packages(host, workgroups, max_iter):
                 torch.cuda.synchronize()
                 eng.run()
                 assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), (sched, run)
+
+
+@pytest.mark.parametrize("w", [1, 15, 17, 31, 33, 63, 65, 511, 513, 1500])
+@pytest.mark.parametrize("rows", [1, 2, 3, 5])
+def test_packages_of_few_rows(rows, w):
+    """Packages of one and two rows are cut into blocks of their own shape: the
+    image in packages of so many rows, and as one package of so few, with a cap
+    where waves take blocks on their own and one where they do not."""
+    with ce.Engine() as eng:
+        for h, cap in ((rows, 100), (301, 100), (301, 5000)):
+            prm = ce.ce_escape_params(w, h, -2.0, -1.5, float(np.float32(3.0 / w)), float(np.float32(3.0 / h)), cap)
+            out = torch.full((h, w), -1, dtype=torch.int32, device="cuda:0")
+            eng.use(ce.CE_DEV_GPU, 0, 0)
+            eng.gpu_workgroups(50 if cap == 5000 else 0)
+            eng.work_items([w, h])
+            eng.program_kernel(ce.CE_KERNEL_ESCAPE, prm)
+            eng.program_out(0, dev=out, nbytes=out.numel() * 4)
+            ref = O.escape(w, h, -2.0, -1.5, prm.dx, prm.dy, cap)
+            for sched in (dict(kind=ce.CE_SCHED_DYNAMIC, package_granules=rows), dict(kind=ce.CE_SCHED_STATIC)):
+                out.fill_(-1)
+                torch.cuda.synchronize()
+                eng.scheduler(**sched)
+                eng.run()
+                assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), (h, cap, sched)
+            out.fill_(-1)
+            torch.cuda.synchronize()
+            ce.ce_bare_run(ce.CE_KERNEL_ESCAPE, prm, [], out)
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), (h, cap)
