@@ -18,7 +18,8 @@ enum SchedKind : uint32_t { kStatic = 0, kDynamic = 1, kHGuided = 2 };
 // 2-D payloads: a tile is kTileRows rows by one column block.
 constexpr uint32_t kEscapeTileRows = 1;
 constexpr uint32_t kEscapeTileCols = 512;
-constexpr uint32_t kBlurTileRows = 32;
+constexpr uint32_t kBlurTileRows = 32;     // at most
+constexpr uint32_t kBlurTileRowBits = 5;  // as a power of two
 constexpr uint32_t kBlurTileCols = 1024;  // 256 threads x 4 columns
 constexpr uint32_t kNbodyGranule = 256;   // bodies per granule (1-D lws)
 constexpr uint32_t kBlockThreads = 256;
@@ -30,7 +31,19 @@ constexpr uint32_t kBlockThreads = 256;
 // 8192 x 4096, the GPU alone, Dynamic, in blocks of 16 x 4 and so: rows of a
 // package 1, max_iter 16, 256, 1000 1245, 1826, 1931 -> 1054, 1135, 1191 us, rows 2
 // 810, 1089, 1159 -> 719, 820, 871; one row of 16.8 million pixels, 256 302 -> 94.
-CE_HD uint32_t escape_block_bits(uint64_t rows) { return rows < 3 ? 7u - (uint32_t)rows : 4u; }
+// `least` (escape_least_bits) is 4 unless the output is written over PCIe.
+CE_HD uint32_t escape_block_bits(uint64_t rows, uint32_t least = 4) {
+  const uint32_t bits = rows < 3 ? 7u - (uint32_t)rows : 4u;
+  return bits < least ? least : bits;
+}
+// Into pinned host memory a wave writes rows of 64 pixels, as far as the image's
+// rows go: the link takes 256 bytes in a row at 55 GB/s, four times 64 at 45 and
+// less where they straddle lines. In blocks of 16 x 4, 32 x 2 and 64 x 1, the GPU
+// alone: 4096^2, max_iter 256 1503, 1304, 1219 us; 4095 x 4097 1813, 1560, 1391;
+// 4096^2, 4000 1546, 1330, 1256; 1024^2, 256 116, 103, 98; 1920 x 1080, 2000 210,
+// 225, 205. Only where the longest orbits set the time it is slower (1920 x 1080,
+// 4000 246, 263, 274).
+CE_HD uint32_t escape_least_bits(uint32_t w, bool host_memory) { return host_memory && w >= 32 ? (w >= 64 ? 6u : 5u) : 4u; }
 
 // Whether the GPU prices binomial calls one per lane (tiles of 64 groups)
 // rather than one group per wave (tiles of four): `groups` is the GPU's share
@@ -236,6 +249,26 @@ CE_HD uint64_t hguided_size(uint64_t G_r, uint64_t P_i, uint64_t sumP, uint32_t 
 CE_HD uint64_t band_edge(uint64_t b, uint64_t G, uint64_t nb) { return nb ? (b * G) / nb : 0; }
 
 CE_HD uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
+
+// Rows of a blur tile, a power of two: halved from 32 until the image has two tiles per compute
+// unit, to no fewer than four, or two where even that leaves compute units
+// without a tile. A wave's rows come one after another, a load's latency
+// each, so short tiles are what a small image needs; a large one needs few
+// halo rows (four per tile). Runs with at least 512, 1024 and 2048
+// tiles asked for: 1024^2 (32 tiles of 32 rows) 25.0 us before, 15.4 with
+// any; 2048^2 25.5 before, 19.1, 20.3, 20.0; 4096^2 34.9 before, 35.0, 36.0,
+// 38.4; 3000 x 4000 41.0 before (also for its last columns), 30.2, 32.2,
+// 35.9; 512^2 in two rows 14.3, in four 14.9, 1000^2 15.7 and 15.4.
+// An image in host memory comes over the link at 50 GB/s, which a few tiles fill,
+// and its halo rows with it: halved only until there are 32 tiles. In rows of 2,
+// 4, 8, 16 and 32: 64^2 18, 22, 28, 41, 68 us; 256^2 33, 29, 31, 40, 61; 512^2 84,
+// 68, 59, 57, 73; 1024^2 305, 213, 177, 178, 169; 2048^2 1037, 779, 595, 481, 430.
+CE_HD uint32_t blur_tile_row_bits(uint32_t w, uint32_t h, bool host_memory) {
+  const uint64_t across = ceil_div(w, kBlurTileCols);
+  uint32_t bits = kBlurTileRowBits;
+  while (bits > 1 && ceil_div(h, 1ull << bits) * across < (host_memory ? 32u : bits > 2 ? 512u : 192u)) --bits;
+  return bits;
+}
 
 // Blocks side by side in a row of w pixels, and one below the other (with shifts:
 // the compiler cannot tell that 64 >> bits is a power of two).

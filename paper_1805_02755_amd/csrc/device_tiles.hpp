@@ -30,9 +30,10 @@ struct EscapeTile {
   static constexpr bool kWavesAlone = true;  // a tile's parts need no barrier between them
   ce_escape_params p;
   uint32_t* out;
-  Divisor across;  // blocks of 16 x 4 side by side
-  __host__ __device__ EscapeTile(const ce_escape_params& params, uint32_t* o)
-      : p(params), out(o), across(escape_blocks_across(params.w, 4)) {}
+  Divisor across;       // blocks of 16 x 4 side by side
+  uint32_t least_bits;  // of a block's columns
+  __host__ __device__ EscapeTile(const ce_escape_params& params, uint32_t* o, bool host_memory)
+      : p(params), out(o), across(escape_blocks_across(params.w, 4)), least_bits(escape_least_bits(params.w, host_memory)) {}
   __device__ void load_constants() {}
   __host__ __device__ uint32_t ncb() const { return (uint32_t)ceil_div(p.w, kEscapeTileCols); }
   __host__ __device__ uint64_t granules() const { return p.h; }
@@ -53,7 +54,7 @@ struct EscapeTile {
       run_part(g0, g1, t, i);
   }
   __device__ __forceinline__ uint32_t blocks(uint64_t g0, uint64_t g1) const {
-    const uint32_t bits = escape_block_bits(g1 - g0);
+    const uint32_t bits = escape_block_bits(g1 - g0, least_bits);
     return escape_blocks_across(p.w, bits) * (uint32_t)escape_blocks_down(g1 - g0, bits);
   }
   // Blocks of a tile, at most, and block i of tile t: a wave's.
@@ -62,7 +63,7 @@ struct EscapeTile {
     return all / nt + (all % nt != 0);
   }
   __device__ __forceinline__ void run_part(uint64_t g0, uint64_t g1, uint32_t t, uint32_t i) const {
-    const uint32_t bits = escape_block_bits(g1 - g0), per_row = escape_blocks_across(p.w, bits), nt = ntiles(g0, g1);
+    const uint32_t bits = escape_block_bits(g1 - g0, least_bits), per_row = escape_blocks_across(p.w, bits), nt = ntiles(g0, g1);
     const uint32_t turn = per_row * 5 / 8 < nt / 8 ? (per_row * 5 / 8) | 1u : nt / 8;
     uint32_t place = t + i * turn;
     while (place >= nt) place -= nt;
@@ -125,6 +126,7 @@ struct Blur5TileT {
   const float* in;
   const float* wt;
   float* out;
+  uint32_t row_bits;  // of a tile's rows (blur_tile_row_bits)
   float w[25];
   __device__ __forceinline__ float uniform_load(const float* a) const {
     if constexpr (kFresh) {
@@ -144,21 +146,7 @@ struct Blur5TileT {
   __host__ __device__ uint32_t ncb() const { return (uint32_t)ceil_div(p.w, kBlurTileCols); }
   __host__ __device__ uint64_t granules() const { return p.h; }
   __host__ __device__ uint32_t ntiles(uint64_t g0, uint64_t g1) const {
-    return (uint32_t)(ceil_div(g1 - g0, tile_rows()) * ncb());
-  }
-  // Rows of a tile: halved from 32 until the image has two tiles per compute
-  // unit, to no fewer than four, or two where even that leaves compute units
-  // without a tile. A wave's rows come one after another, a load's latency
-  // each, so short tiles are what a small image needs; a large one needs few
-  // halo rows (four per tile). Runs with at least 512, 1024 and 2048
-  // tiles asked for: 1024^2 (32 tiles of 32 rows) 25.0 us before, 15.4 with
-  // any; 2048^2 25.5 before, 19.1, 20.3, 20.0; 4096^2 34.9 before, 35.0, 36.0,
-  // 38.4; 3000 x 4000 41.0 before (also for its last columns), 30.2, 32.2,
-  // 35.9; 512^2 in two rows 14.3, in four 14.9, 1000^2 15.7 and 15.4.
-  __host__ __device__ uint32_t tile_rows() const {
-    uint32_t r = kBlurTileRows;
-    while (r > 2 && ceil_div(p.h, r) * ncb() < (r > 4 ? 512u : 192u)) r /= 2;
-    return r;
+    return (uint32_t)((g1 - g0 + ((1u << row_bits) - 1u)) >> row_bits) * ncb();
   }
   __device__ __forceinline__ const float* row_ptr(int64_t yy) const {
     yy = yy < 0 ? 0 : (yy >= (int64_t)p.h ? (int64_t)p.h - 1 : yy);
@@ -268,9 +256,9 @@ struct Blur5TileT {
   }
 
   __device__ void run(uint64_t g0, uint64_t g1, uint32_t t) const {
-    const uint32_t nc = ncb(), rows = tile_rows();
-    const uint64_t r0 = g0 + (uint64_t)(t / nc) * rows;
-    const uint64_t r1 = (r0 + rows < g1) ? r0 + rows : g1;
+    const uint32_t nc = ncb();
+    const uint64_t r0 = g0 + ((uint64_t)(t / nc) << row_bits), end = r0 + (1u << row_bits);
+    const uint64_t r1 = end < g1 ? end : g1;
     // first column of this wave (uniform) and of this lane
     const uint32_t tid = thread_index();
     const uint32_t xw = (t % nc) * kBlurTileCols + (__builtin_amdgcn_readfirstlane(tid) & ~63u) * 4u;

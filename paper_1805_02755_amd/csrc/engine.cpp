@@ -1060,6 +1060,7 @@ struct ce_engine {
     kargs.out = gpu_out[0];
     kargs.out1 = gpu_out[1];
     for (int s = 0; s < n_out_slots(); ++s) pcie_stream |= use_gpu() && gpu_out[s] && gpu_out[s] == out[s].host_dev;
+    kargs.host_memory = pcie_stream;
     if (kernel_id == CE_KERNEL_RUNTIME) {
       // generic arguments: inputs, then outputs, then the scalar block
       for (uint32_t k = 0; k < rt_n_in; ++k) kargs.rt.buf[k] = const_cast<void*>(gin[k]);
@@ -1339,7 +1340,8 @@ struct ce_engine {
       // out and the rest leave at once; a caller's workgroups all take part.
       const bool sweep = light_exit && gs.pre_only && kernel_id == CE_KERNEL_ESCAPE;
       if (sweep) {
-        const uint64_t rows = gs.pre_g1 - gs.pre_g0, bits = escape_block_bits(rows);
+        const uint64_t rows = gs.pre_g1 - gs.pre_g0;
+        const uint32_t bits = escape_block_bits(rows, escape_least_bits(esc.w, pcie_stream));
         const uint64_t blocks = escape_blocks_across(esc.w, bits) * escape_blocks_down(rows, bits);
         sweepers = grid_override ? grid : sweep_workers(gs.pre_nt, blocks, resident_wgs);
         const bool per_tile = gs.pre_nt > kDirectOneShotRounds * (uint64_t)resident_wgs && gs.pre_nt <= kFastExitMaxWgs;

@@ -164,9 +164,9 @@ void launch_nbody_bare(const T& pay, uint64_t G, uint32_t tiles, hipStream_t st)
     hipLaunchKernelGGL(k_bare<T>, dim3(tiles), dim3(kBlockThreads), 0, st, pay, G);
   }
 }
-EscapeTile make_escape(const KernelArgs& a) { return EscapeTile(a.esc, (uint32_t*)a.out); }
+EscapeTile make_escape(const KernelArgs& a) { return EscapeTile(a.esc, (uint32_t*)a.out, a.host_memory); }
 Blur5Tile make_blur(const KernelArgs& a) {
-  return Blur5Tile{a.blur, (const float*)a.in0, (const float*)a.in1, (float*)a.out, {}};
+  return Blur5Tile{a.blur, (const float*)a.in0, (const float*)a.in1, (float*)a.out, blur_tile_row_bits(a.blur.w, a.blur.h, a.host_memory), {}};
 }
 template <bool S>
 NbodyTile<S> make_nbody(const KernelArgs& a) {
@@ -275,7 +275,7 @@ hipError_t launch_direct(const KernelArgs& a, const DirectArgs& d, uint32_t grid
   const dim3 g(grid), b(kBlockThreads);
   switch (a.kernel_id) {
     case CE_KERNEL_ESCAPE: {
-      const uint32_t bits = escape_block_bits(d.g1 - d.g0);
+      const uint32_t bits = escape_block_bits(d.g1 - d.g0, escape_least_bits(a.esc.w, a.host_memory));
       const uint64_t per_row = escape_blocks_across(a.esc.w, bits), blocks = per_row * escape_blocks_down(d.g1 - d.g0, bits);
       if (blocks >= (1ull << 30)) {
         hipLaunchKernelGGL(k_direct<EscapeTile>, g, b, 0, st, make_escape(a), d);

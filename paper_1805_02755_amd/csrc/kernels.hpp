@@ -25,6 +25,7 @@ struct KernelArgs {
   const void* in1;
   void* out;
   void* out1;               // second output (n-body step: velocities)
+  bool host_memory;         // some of these are pinned host memory, read or written over PCIe
   // payload supplied at run time: device arguments, index space and the
   // loaded module's kernels (hipFunction_t)
   ce_rt_args rt;

@@ -343,20 +343,26 @@ struct ce_server {
     return CE_OK;
   }
 
+  // What a job's descriptor says of it before it has memory.
+  static ServeDesc plan_of(const ce_job& job) {
+    ServeDesc d{};
+    d.kind = (uint32_t)job.kernel_id;
+    d.esc = job.esc;
+    d.blur = job.blur;
+    d.nb = job.nb;
+    d.strict = job.nb.strict;
+    serve_plan(d);
+    return d;
+  }
+
   // Admission: the oldest pending job goes in when a slot and memory are free.
   bool admit_one(std::unique_lock<std::mutex>& lk) {
     if (pending.empty() || !session_on) return false;
     if (inflight.size() >= cfg.max_inflight || head >= cfg.max_jobs) return false;
     const uint64_t tk = pending.front();
     JobRec& r = jobs[tk];
-    {
-      ServeDesc probe{};
-      probe.kind = (uint32_t)r.job.kernel_id;
-      probe.esc = r.job.esc;
-      probe.blur = r.job.blur;
-      probe.nb = r.job.nb;
-      if (session_tiles + serve_tiles(probe) > kServeTotalMask) return false;  // waits for the next session
-    }
+    ServeDesc d = plan_of(r.job);
+    if (session_tiles + d.ntiles > kServeTotalMask) return false;  // waits for the next session
     const size_t ob = out_bytes_of(r.job);
     size_t need = (ob + 255) & ~(size_t)255;
     const bool copy0 = !r.job.in0_dev && in_bytes_of(r.job, 0);
@@ -372,17 +378,9 @@ struct ce_server {
     r.has_mem = true;
     r.out_bytes = ob;
     char* mem = arena.base + off;
-    ServeDesc d{};
-    d.kind = (uint32_t)r.job.kernel_id;
-    d.esc = r.job.esc;
-    d.blur = r.job.blur;
-    d.nb = r.job.nb;
-    d.strict = r.job.nb.strict;
     d.out = mem;
     d.in0 = copy0 ? (const void*)(mem + ((ob + 255) & ~(size_t)255)) : r.job.in0_dev;
     d.in1 = copy1 ? (const void*)(mem + ((ob + 255) & ~(size_t)255) + i0) : r.job.in1_dev;
-    d.granules = serve_granules(d);
-    d.ntiles = serve_tiles(d);
     d.seq = head;
     lk.unlock();
     std::unique_lock<std::mutex> ck(copy_mu);
@@ -516,12 +514,7 @@ struct ce_server {
   bool next_fits_tiles() const {
     if (pending.empty()) return true;
     const JobRec& r = jobs[pending.front()];
-    ServeDesc probe{};
-    probe.kind = (uint32_t)r.job.kernel_id;
-    probe.esc = r.job.esc;
-    probe.blur = r.job.blur;
-    probe.nb = r.job.nb;
-    return session_tiles + serve_tiles(probe) <= kServeTotalMask;
+    return session_tiles + plan_of(r.job).ntiles <= kServeTotalMask;
   }
 
   void loop() {

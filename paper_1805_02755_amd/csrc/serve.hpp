@@ -22,7 +22,7 @@ struct alignas(128) ServeDesc {
   ce_escape_params esc;  // 28 B
   ce_blur5_params blur;  // 8 B
   ce_nbody_params nb;    // 12 B
-  uint32_t pad1;
+  uint32_t row_bits;     // blur: rows of a tile, as a power of two
   const void* in0;
   const void* in1;
   void* out;
@@ -70,8 +70,7 @@ struct ServeArgs {
   uint64_t idle_ticks;    // the kernel leaves after this many ticks with no new job
 };
 
-uint32_t serve_tiles(const ServeDesc& d);  // GPU tiles of a job
-uint64_t serve_granules(const ServeDesc& d);
+void serve_plan(ServeDesc& d);  // sets granules, ntiles and what else says how the job is cut
 hipError_t serve_blocks_per_cu(int* blocks);
 hipError_t launch_serve(const ServeArgs& a, uint32_t grid, hipStream_t st);
 

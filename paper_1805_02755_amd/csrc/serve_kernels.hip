@@ -125,10 +125,10 @@ __device__ bool serve_next(const ServeArgs& a, uint64_t t_start, uint32_t* p_cac
 __device__ void serve_tile(const ServeDesc& d, uint32_t ti) {
   const uint32_t kind = __builtin_amdgcn_readfirstlane(d.kind);
   if (kind == CE_KERNEL_ESCAPE) {
-    EscapeTile e(d.esc, (uint32_t*)d.out);
+    EscapeTile e(d.esc, (uint32_t*)d.out, false);
     e.run(0, d.granules, ti);
   } else if (kind == CE_KERNEL_BLUR5) {
-    Blur5TileFresh b{d.blur, (const float*)d.in0, (const float*)d.in1, (float*)d.out, {}};
+    Blur5TileFresh b{d.blur, (const float*)d.in0, (const float*)d.in1, (float*)d.out, d.row_bits, {}};
     b.load_constants();
     b.run(0, d.granules, ti);
   } else if (__builtin_amdgcn_readfirstlane(d.strict)) {
@@ -203,24 +203,23 @@ __global__ __launch_bounds__(kBlockThreads, 5) void k_serve(ServeArgs a) {
   }
 }
 
-uint32_t serve_tiles(const ServeDesc& d) {
+void serve_plan(ServeDesc& d) {
+  d.granules = d.ntiles = d.row_bits = 0;
   switch (d.kind) {
-    case CE_KERNEL_ESCAPE: return EscapeTile(d.esc, nullptr).ntiles(0, d.esc.h);
-    case CE_KERNEL_BLUR5: return Blur5Tile{d.blur, nullptr, nullptr, nullptr, {}}.ntiles(0, d.blur.h);
+    case CE_KERNEL_ESCAPE:
+      d.granules = d.esc.h;
+      d.ntiles = EscapeTile(d.esc, nullptr, false).ntiles(0, d.granules);
+      break;
+    case CE_KERNEL_BLUR5:
+      d.granules = d.blur.h;
+      d.row_bits = blur_tile_row_bits(d.blur.w, d.blur.h, false);
+      d.ntiles = Blur5Tile{d.blur, nullptr, nullptr, nullptr, d.row_bits, {}}.ntiles(0, d.granules);
+      break;
     case CE_KERNEL_NBODY_ACC:
-      return d.nb.n >= kServeWholeBodies ? (uint32_t)ceil_div(d.nb.n, kNbodyGranule)
-                                         : nbody_tiles(d.nb.n, 0, ceil_div(d.nb.n, kNbodyGranule));
+      d.granules = ceil_div(d.nb.n, kNbodyGranule);
+      d.ntiles = d.nb.n >= kServeWholeBodies ? (uint32_t)d.granules : nbody_tiles(d.nb.n, 0, d.granules);
+      break;
   }
-  return 0;
-}
-
-uint64_t serve_granules(const ServeDesc& d) {
-  switch (d.kind) {
-    case CE_KERNEL_ESCAPE: return d.esc.h;
-    case CE_KERNEL_BLUR5: return d.blur.h;
-    case CE_KERNEL_NBODY_ACC: return ceil_div(d.nb.n, kNbodyGranule);
-  }
-  return 0;
 }
 
 hipError_t serve_blocks_per_cu(int* blocks) {

@@ -41,3 +41,35 @@ def test_blocks_cover_the_package_without_padding_rows(tmp_path, w):
             assert down * high == rows
         rows_seen += 1
     assert rows_seen == 40
+
+
+HOST_SRC = r"""
+#include <cstdio>
+#include "common.hpp"
+int main() {
+  const uint32_t sides[][2] = {{1, 1}, {31, 400}, {32, 400}, {63, 400}, {64, 64}, {200, 200}, {512, 512}, {1024, 1024},
+                               {2048, 2048}, {4099, 3001}, {100, 100000}, {8192, 8192}};
+  for (auto& s : sides) {
+    const uint32_t bits = ce::blur_tile_row_bits(s[0], s[1], true);
+    printf("%u %u %u %u %llu\n", s[0], s[1], ce::escape_block_bits(400, ce::escape_least_bits(s[0], true)), 1u << bits,
+           (unsigned long long)(ce::ceil_div(s[1], 1ull << bits) * ce::ceil_div(s[0], ce::kBlurTileCols)));
+  }
+}
+"""
+
+
+def test_tiles_of_host_memory_suit_the_link(tmp_path):
+    """Buffers in pinned host memory: escape-time blocks are rows of 64 pixels as
+    far as the image is that wide, and blur tiles short only until there are
+    32 of them (each reads four halo rows over the link)."""
+    src = tmp_path / "host.cpp"
+    src.write_text(HOST_SRC)
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", str(tmp_path / "host"), str(src)], check=True)
+    out = subprocess.run([str(tmp_path / "host")], check=True, capture_output=True, text=True).stdout
+    lines = [[int(x) for x in line.split()] for line in out.splitlines()]
+    assert len(lines) == 12
+    for w, h, bits, rows, tiles in lines:
+        assert bits == (6 if w >= 64 else 5 if w >= 32 else 4)
+        assert rows in (2, 4, 8, 16, 32)
+        assert rows == 32 or tiles < 64
+        assert rows == 2 or tiles >= 32

@@ -70,3 +70,21 @@ def test_blur_full_size_pinned(eng):
                               np.float32, BOTH, "hguided", mode="pinned")
     assert np.array_equal(out.view(np.uint32), ref.view(np.uint32)), diff_report(out, ref, tr)
     check_trace(tr, h, 2)
+
+
+@pytest.mark.parametrize("w,h", [(1, 300), (31, 300), (32, 301), (40, 33), (63, 200), (64, 200), (65, 3), (513, 130)])
+def test_block_and_tile_shapes_pinned(eng, w, h):
+    """Widths around the wave's row of pixels that host memory takes, and blur
+    tiles of every height that images of few tiles take."""
+    p = synth.escape_region(w, h, -2.0, 0.6, -1.2, 1.2, 3000)
+    ref = O.escape(p.w, p.h, *[float(v) for v in p.as_f32()], p.max_iter)
+    img = synth.blur_image(w, h, seed=w + h)
+    wt = ce.ce_gauss5_weights(1.0)
+    blurred = O.blur5(img, O.gauss5_weights(1.0))
+    for devs, sched in ((ce.CE_DEV_GPU, "static"), (ce.CE_DEV_GPU, "dynamic"), (BOTH, "hguided")):
+        out, st, tr = run_payload(eng, ce.CE_KERNEL_ESCAPE, escape_params(p), [w, h], None, [], (h, w), np.uint32,
+                                  devs, sched, mode="pinned")
+        assert np.array_equal(out, ref), (sched, diff_report(out, ref, tr))
+        out, st, tr = run_payload(eng, ce.CE_KERNEL_BLUR5, ce.ce_blur5_params(w, h), [w, h], None, [img, wt], (h, w),
+                                  np.float32, devs, sched, mode="pinned")
+        assert np.array_equal(out.view(np.uint32), blurred.view(np.uint32)), (sched, diff_report(out, blurred, tr))
