@@ -212,7 +212,11 @@ void serve_plan(ServeDesc& d) {
       break;
     case CE_KERNEL_BLUR5:
       d.granules = d.blur.h;
-      d.row_bits = blur_tile_row_bits(d.blur.w, d.blur.h, false);
+      // 32 rows whatever the image: every tile takes a ticket from one counter,
+      // which sets the time of many jobs (64 of 1024^2 555 us; by image size, as in
+      // the engine, 1935), and one job gains nothing (256^2 93 and 89, 2048^2 116
+      // and 152).
+      d.row_bits = kBlurTileRowBits;
       d.ntiles = Blur5Tile{d.blur, nullptr, nullptr, nullptr, d.row_bits, {}}.ntiles(0, d.granules);
       break;
     case CE_KERNEL_NBODY_ACC:
