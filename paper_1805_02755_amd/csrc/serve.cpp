@@ -343,15 +343,18 @@ struct ce_server {
     return CE_OK;
   }
 
-  // What a job's descriptor says of it before it has memory.
-  static ServeDesc plan_of(const ce_job& job) {
+  // What the descriptor of a job to be admitted now says before it has memory.
+  ServeDesc plan_of(const ce_job& job) const {
+    uint64_t busy = 0;
+    for (const uint64_t tk : inflight)
+      if (jobs[tk].job.kernel_id == CE_KERNEL_NBODY_ACC) busy += jobs[tk].desc.granules;
     ServeDesc d{};
     d.kind = (uint32_t)job.kernel_id;
     d.esc = job.esc;
     d.blur = job.blur;
     d.nb = job.nb;
     d.strict = job.nb.strict;
-    serve_plan(d);
+    serve_plan(d, busy);
     return d;
   }
 

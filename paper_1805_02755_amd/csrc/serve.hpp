@@ -22,7 +22,7 @@ struct alignas(128) ServeDesc {
   ce_escape_params esc;  // 28 B
   ce_blur5_params blur;  // 8 B
   ce_nbody_params nb;    // 12 B
-  uint32_t row_bits;     // blur: rows of a tile, as a power of two
+  uint32_t form;         // of the tiles: blur, their rows as a power of two; n-body, 1: whole granules
   const void* in0;
   const void* in1;
   void* out;
@@ -70,7 +70,9 @@ struct ServeArgs {
   uint64_t idle_ticks;    // the kernel leaves after this many ticks with no new job
 };
 
-void serve_plan(ServeDesc& d);  // sets granules, ntiles and what else says how the job is cut
+// Cuts the job into tiles (granules, ntiles, form), with `busy` granules of other
+// n-body jobs in flight.
+void serve_plan(ServeDesc& d, uint64_t busy);
 hipError_t serve_blocks_per_cu(int* blocks);
 hipError_t launch_serve(const ServeArgs& a, uint32_t grid, hipStream_t st);
 

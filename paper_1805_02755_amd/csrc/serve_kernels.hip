@@ -20,12 +20,16 @@ namespace {
 
 constexpr uint32_t kDescWords = sizeof(ServeDesc) / 8;
 
-// N-body jobs of fewer bodies than this run in groups of 64 bodies, so that a
-// job alone on the GPU uses more than a few compute units; larger ones with
-// one thread per body, which takes fewer instructions when the GPU is full.
+// N-body jobs run in groups of 64 bodies while the jobs in flight, with this one,
+// hold no more granules than four per compute unit, so that few jobs use more than
+// some of the compute units; beyond that with one thread per body, which takes
+// fewer instructions when the GPU is full. Strict, in us, groups and whole
+// granules for all jobs: 1 of 4,096 bodies 162 and 283, 16 302 and 452, 64 734 and
+// 758, 4 of 16,384 726 and 1385, 128 of 8,192 3968 and 3446, 64 of 20,000 11050
+// and 9630 (decided so 10646).
 // The groups' chunks are shorter than the engine's, which would leave the
 // kernel four workgroups per compute unit instead of five.
-constexpr uint32_t kServeWholeBodies = 32768;
+constexpr uint64_t kServeGroupGranules = 1024;
 constexpr uint32_t kServeNbodyChunk = 8;
 constexpr uint32_t kServeNbodyLds = sizeof(f32x4[2 * kNbodyWhole]);
 
@@ -33,7 +37,7 @@ template <bool STRICT>
 __device__ void serve_nbody(const ServeDesc& d, uint32_t ti) {
   const ce_nbody_params nb{(uint32_t)__builtin_amdgcn_readfirstlane(d.nb.n), d.nb.eps2, d.nb.strict};
   const NbodyTile<STRICT> t{nb, (const float4*)d.in0, (float4*)d.out};
-  if (nb.n >= kServeWholeBodies)  // uniform: both forms hold barriers
+  if (__builtin_amdgcn_readfirstlane(d.form) != 0)  // uniform: both forms hold barriers
     t.template run_whole<kServeNbodyLds>(0, ti);
   else
     t.template run_group<kBlockThreads / 64, kServeNbodyChunk, kServeNbodyLds>(0, ti);
@@ -128,7 +132,7 @@ __device__ void serve_tile(const ServeDesc& d, uint32_t ti) {
     EscapeTile e(d.esc, (uint32_t*)d.out, false);
     e.run(0, d.granules, ti);
   } else if (kind == CE_KERNEL_BLUR5) {
-    Blur5TileFresh b{d.blur, (const float*)d.in0, (const float*)d.in1, (float*)d.out, d.row_bits, {}};
+    Blur5TileFresh b{d.blur, (const float*)d.in0, (const float*)d.in1, (float*)d.out, (uint32_t)__builtin_amdgcn_readfirstlane(d.form), {}};
     b.load_constants();
     b.run(0, d.granules, ti);
   } else if (__builtin_amdgcn_readfirstlane(d.strict)) {
@@ -203,8 +207,8 @@ __global__ __launch_bounds__(kBlockThreads, 5) void k_serve(ServeArgs a) {
   }
 }
 
-void serve_plan(ServeDesc& d) {
-  d.granules = d.ntiles = d.row_bits = 0;
+void serve_plan(ServeDesc& d, uint64_t busy) {
+  d.granules = d.ntiles = d.form = 0;
   switch (d.kind) {
     case CE_KERNEL_ESCAPE:
       d.granules = d.esc.h;
@@ -216,12 +220,13 @@ void serve_plan(ServeDesc& d) {
       // which sets the time of many jobs (64 of 1024^2 555 us; by image size, as in
       // the engine, 1935), and one job gains nothing (256^2 93 and 89, 2048^2 116
       // and 152).
-      d.row_bits = kBlurTileRowBits;
-      d.ntiles = Blur5Tile{d.blur, nullptr, nullptr, nullptr, d.row_bits, {}}.ntiles(0, d.granules);
+      d.form = kBlurTileRowBits;
+      d.ntiles = Blur5Tile{d.blur, nullptr, nullptr, nullptr, d.form, {}}.ntiles(0, d.granules);
       break;
     case CE_KERNEL_NBODY_ACC:
       d.granules = ceil_div(d.nb.n, kNbodyGranule);
-      d.ntiles = d.nb.n >= kServeWholeBodies ? (uint32_t)d.granules : nbody_tiles(d.nb.n, 0, d.granules);
+      d.form = busy + d.granules > kServeGroupGranules;
+      d.ntiles = d.form ? (uint32_t)d.granules : nbody_tiles(d.nb.n, 0, d.granules);
       break;
   }
 }

@@ -272,3 +272,22 @@ def test_many_blur_jobs_are_not_bound_by_their_tickets():
                 srv.release(t)
     assert np.array_equal(out.view(np.uint32), O.blur5(img, O.gauss5_weights(1.0)).view(np.uint32))
     assert best < 120_000, best * 1e-8
+
+
+def test_nbody_jobs_in_both_forms():
+    """Jobs in groups and, once the GPU is full, in whole granules: 40 jobs of 8,000
+    to 8,039 bodies are more than the granules up to which a job takes groups.
+    Sampled bodies of each equal the oracle's."""
+    pos = synth.nbody_bodies(8039, seed=8)
+    pos_d = torch.from_numpy(pos).to(DEV)
+    torch.cuda.synchronize()
+    with ce.Server(1 << 30, keep_outputs=True, session_timeout_s=30.0) as srv:
+        ts = [(n, srv.submit(ce.CE_KERNEL_NBODY_ACC, ce.ce_nbody_params(n, 1e-6, 1), pos_d)) for n in range(8000, 8040)]
+        srv.drain(60.0)
+        for n, t in ts:
+            out = np.full((n, 4), np.nan, np.float32)
+            srv.copy_output(t, out)
+            assert not np.isnan(out).any(), n
+            for i in (0, 63, 64, 255, 256, n // 2, n - 1):
+                ref = O.nbody_acc_body(pos[:n], 1e-6, i, True)
+                assert np.array_equal(out[i].view(np.uint32), ref.view(np.uint32)), (n, i)
