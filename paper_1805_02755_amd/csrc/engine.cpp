@@ -44,7 +44,10 @@ inline void cpu_relax() { _mm_pause(); }
 
 constexpr uint32_t kHostNbodyTile = 16;  // bodies per host tile
 constexpr int kMaxSlots = 2;
-constexpr uint64_t kDeepEscape = 6144;  // tiles per workgroup times max_iter
+// How escape-time tiles are dealt (run_impl)
+constexpr uint64_t kDeepEscape = 6144;    // tiles per workgroup times max_iter
+constexpr uint64_t kLargeEscape = 65536;  // tiles
+constexpr uint64_t kManyBands = 32;       // of a Static plan
 // Bounds on the waits inside the GPU kernel: every kernel ends, so the host
 // can wait for it with a plain stream synchronisation.
 constexpr uint64_t kDispenserWaitSeconds = 5;
@@ -1232,11 +1235,7 @@ struct ce_engine {
       // blocks of pixels lie all over their package, nearly: a fixed
       // round-robin needs no atomics, and a workgroup runs its tiles of a
       // package one after another, its waves not waiting for each other in
-      // between (next_tile). Escape-time co-executed under HGuided, against
-      // atomic tickets and a barrier per tile: 2048^2 with max_iter 256 62
-      // against 92 us, 1920 x 1080 with 1000 171 against 205, 4096^2 with 256
-      // 206 against 185 and, with the host slower, 172 against 183 (deep caps:
-      // below). With gatherers sharing some CUs the fixed
+      // between (next_tile). With gatherers sharing some CUs the fixed
       // round-robin would leave the workgroups on those CUs behind, so tiles
       // are dealt dynamically then.
       // A binomial tile runs for tens of microseconds, so one atomic per tile
@@ -1246,27 +1245,37 @@ struct ce_engine {
       // share of tickets and run them on an otherwise idle GPU.
       const bool long_tiles = kernel_id == CE_KERNEL_BINOMIAL;
       if (long_tiles) gs.chunk = 1;
+      const uint64_t all_tiles = gpu_tiles(kargs, 0, G), wgs = grid - gather_wgs;
+      // Escape-time takes one of three ways. In us, HGuided, Dynamic with packages
+      // of 64 rows and Static in 8 and 64 bands, the GPU alone:
+      //                         round-robin          tickets              waves alone
+      //   2048^2,  cap 64       48   73   54  172    86   92   85  162    84   91   86  165
+      //   4096^2,  64          122  233  120  229   156  195  151  196   146  206  153  196
+      //   8192^2,  64          407  792  364  558   312  606  303  329   406  640  402  446
+      //   3000 x 2001, 64      139  268  127  312   191  354  152  179   205  365  172  205
+      //   8192^2,  256         612  854  485  754   369  611  364  409   441  664  442  481
+      //   1920 x 1080, 1000    140  203  200  276   153  175  168  251   106  129  125  162
+      //   4096^2,  1000        351  315  274  300   210  299  230  306   180  241  195  242
+      //   8192^2,  4000       2322 1851 2108 3436  1154 1551 1126 1276   807  972  835  979
+      // Deep: the blocks that run to a deep cap (some tens of microseconds each)
+      // are few, and under the round-robin the workgroups that own more of them set
+      // the time of the run, as the wave that has one does for its workgroup in
+      // every package. So tickets are atomic, and the waves take blocks on their
+      // own (WaveDealer), from two tiles per workgroup on and where tiles per
+      // workgroup times max_iter is large enough to pay for both.
+      // Large: over many tiles what one workgroup's cost more than another's adds
+      // up, and the atomics, one for several tiles, are few beside the work; and in
+      // many bands a workgroup has few tiles of each, which under the round-robin
+      // it looks up one by one.
+      const bool escape = kernel_id == CE_KERNEL_ESCAPE, large = escape && all_tiles > kLargeEscape;
+      const bool deep = escape && per_wg >= 2 && kargs.esc.max_iter >= (large ? 512u : 256u) &&
+                        per_wg * kargs.esc.max_iter >= kDeepEscape;
+      const bool many_bands = escape && gs.kind == kStatic && gs.st_nbands >= kManyBands;
       // A payload supplied at run time has tiles of unknown cost: beyond one
-      // round they are dealt by atomic tickets. Within one round every
+      // round they are dealt by atomic tickets too. Within one round every
       // workgroup runs one tile either way, and the round-robin needs no
       // atomic.
-      const bool uneven = kernel_id == CE_KERNEL_RUNTIME && gpu_tiles(kargs, 0, G) > (uint64_t)(grid - gather_wgs);
-      // Escape-time with a deep cap: the blocks that run to it (some tens of
-      // microseconds each) are few, and under the round-robin the workgroups
-      // that own more of them set the time of the run, as the wave that has one
-      // does for its workgroup in every package. So tickets are atomic, and the
-      // waves take blocks on their own (WaveDealer), from two tiles per
-      // workgroup on and where tiles per workgroup times max_iter is large
-      // enough to pay for both. Co-executed under HGuided, against the
-      // round-robin and a barrier per package: 8192^2 with max_iter 4096 845
-      // against 2133 us, with 256 461 against 492; 4096^2 with 1000 212 against
-      // 273; 3000^2 with 2000 423 against 498; 1920 x 1080 with 4096 208
-      // against 454; 1500^2 with 4096 151 against 251. Below: 2048^2 with 1000
-      // (4,000) 102.5 against 101.5, with 512 92 against 76; 3000 x 2001 with
-      // 512 237 against 225; 8192^2 with 100 436 against 430, with 64 428
-      // against 358.
-      const bool deep = kernel_id == CE_KERNEL_ESCAPE && per_wg >= 2 && kargs.esc.max_iter >= 256 &&
-                        per_wg * kargs.esc.max_iter >= kDeepEscape;
+      const bool uneven = (kernel_id == CE_KERNEL_RUNTIME || large || many_bands) && all_tiles > wgs;
       gs.waves_alone = deep ? 1u : 0u;
       gs.stride = (gather || long_tiles || uneven || deep) ? 0u : 1u;
       // the gatherers wait for the host's packages, whose length depends on the problem

@@ -154,3 +154,28 @@ def test_packages_of_few_rows(rows, w):
             torch.cuda.synchronize()
             ce.ce_bare_run(ce.CE_KERNEL_ESCAPE, prm, [], out)
             assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), (h, cap)
+
+
+@pytest.mark.parametrize("cap", [64, 300, 600])
+@pytest.mark.parametrize("w,h", [(3, 65536), (3, 65537), (515, 40000), (700, 300)])
+def test_many_tiles_and_many_bands(w, h, cap):
+    """Around 65,536 tiles, and in 31, 32 and 64 bands, where tiles go from the
+    round-robin to tickets, with caps on either side of the one from which waves
+    take blocks on their own."""
+    prm = ce.ce_escape_params(w, h, -2.0, -1.5, float(np.float32(3.0 / w)), float(np.float32(3.0 / h)), cap)
+    ref = O.escape(w, h, -2.0, -1.5, prm.dx, prm.dy, cap)
+    out = torch.empty((h, w), dtype=torch.int32, device="cuda:0")
+    with ce.Engine() as eng:
+        eng.use(ce.CE_DEV_GPU, 0, 0)
+        eng.work_items([w, h])
+        eng.program_kernel(ce.CE_KERNEL_ESCAPE, prm)
+        eng.program_out(0, dev=out, nbytes=out.numel() * 4)
+        for sched in (dict(kind=ce.CE_SCHED_HGUIDED, k=2, power=[1]), dict(kind=ce.CE_SCHED_DYNAMIC, n_packages=50),
+                      dict(kind=ce.CE_SCHED_STATIC, n_packages=31), dict(kind=ce.CE_SCHED_STATIC, n_packages=32),
+                      dict(kind=ce.CE_SCHED_STATIC, n_packages=64)):
+            eng.scheduler(**sched)
+            for _ in range(2):
+                out.fill_(-1)
+                torch.cuda.synchronize()
+                eng.run()
+                assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), sched
