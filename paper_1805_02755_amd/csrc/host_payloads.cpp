@@ -293,7 +293,7 @@ void nbody_step_update(const float* pos4, const float* vel4, float dt, uint64_t 
 
 void binomial_groups(const float* spots4, const float* factors, uint32_t steps, float strike, float pu, float pd,
                      uint64_t g0, uint64_t g1, float* out4) {
-  float v[256];
+  alignas(64) float v[256];
   for (uint64_t g = g0; g < g1; ++g) {
     for (int c = 0; c < 4; ++c) {
       const float S = spots4[4 * g + c];
