@@ -47,10 +47,11 @@ CE_HD uint32_t escape_least_bits(uint32_t w, bool host_memory) { return host_mem
 
 // Whether the GPU prices binomial calls one per lane (tiles of 64 groups)
 // rather than one group per wave (tiles of four): `groups` is the GPU's share
-// of the index space and `package` the smallest package it may be handed. A
-// call-form tile takes as long whether it holds 64 groups or one, so packages
-// of fewer than 512 would be mostly padding; and below 16,384 groups it leaves
-// SIMDs idle (16,384 groups of 254 steps: about 190 us against 205 in the
+// of the index space and `package` the smallest package it may be handed, where
+// the caller says so (binomial_by_call in the engine: not under HGuided without a
+// minimum). A call-form tile takes as long whether it holds 64 groups or one, so
+// packages of fewer than 512 would be mostly padding; and below 16,384 groups it
+// leaves SIMDs idle (16,384 groups of 254 steps: about 190 us against 205 in the
 // group form; 8,192: 188 against 120).
 CE_HD bool binomial_call_form(uint64_t groups, uint64_t package) { return groups >= 16384 && package >= 512; }
 
