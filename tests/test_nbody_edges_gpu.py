@@ -164,3 +164,51 @@ def test_static_share_of_the_gpu_around_whole_granules(eng, n, strict, kind):
             assert np.all(np.abs(got[0][i, :3] - (x + v * dt + a * h)) <= bound * h + slack), (share, i)
             slack = 2.0 ** -22 * (np.abs(v) + np.abs(a * dt) + bound * dt)
             assert np.all(np.abs(got[1][i, :3] - (v + a * dt)) <= bound * dt + slack), (share, i)
+
+
+def gpu_runs(eng, kid, prm, ins, n, n_out):
+    """The payload's outputs in the plain launch, on the GPU alone and in packages."""
+    outs = [torch.empty((n, 4), device=DEV) for _ in range(n_out)]
+    for name, sched in (("plain", None), ("direct", dict(kind=ce.CE_SCHED_STATIC)),
+                        ("persistent", dict(kind=ce.CE_SCHED_DYNAMIC, package_granules=1))):
+        for o in outs:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        if sched is None:
+            ce.ce_bare_run_outs(kid, prm, ins, outs)
+        else:
+            eng.use(ce.CE_DEV_GPU, 0, 0)
+            eng.work_items([n], [256])
+            eng.scheduler(**sched)
+            eng.program_kernel(kid, prm)
+            for s, t in enumerate(ins):
+                eng.program_in(s, dev=t, nbytes=n * 16)
+            for s, o in enumerate(outs):
+                eng.program_out(s, dev=o, nbytes=n * 16)
+            eng.run()
+        yield name, [o.cpu().numpy() for o in outs]
+
+
+@pytest.mark.parametrize("n", BORDERS)
+def test_borders_of_the_hardware_rsqrt_and_the_step(eng, n):
+    """What the borders above leave out: the hardware 1/sqrt, whose whole granules
+    begin elsewhere, and the step's own stores in either."""
+    pos, vel = synth.nbody_bodies(n, seed=n + 1), synth.nbody_velocities(n, seed=n + 1)
+    p_d, v_d = torch.from_numpy(pos).to(DEV), torch.from_numpy(vel).to(DEV)
+    dt = 0.002
+    at = sorted({0, 63, 64, n // 2, n - 65, n - 2, n - 1})
+    bounds = {i: bound_f64(pos, i) for i in at}
+    for name, (a,) in gpu_runs(eng, ce.CE_KERNEL_NBODY_ACC, ce.ce_nbody_params(n, EPS2, 0), [p_d], n, 1):
+        assert not np.isnan(a).any(), name
+        assert all(np.linalg.norm(a[i, :3] - bounds[i][0]) <= bounds[i][1] for i in at), name
+    steps = {i: O.nbody_step_body(pos, vel, EPS2, dt, i, True) for i in at}
+    for name, (x, v) in gpu_runs(eng, ce.CE_KERNEL_NBODY_STEP, ce.ce_nbody_step_params(n, EPS2, dt, 1), [p_d, v_d], n, 2):
+        assert not np.isnan(x).any() and not np.isnan(v).any(), name
+        assert all(same(x[i], steps[i][0]) and same(v[i], steps[i][1]) for i in at), name
+    for name, (x, v) in gpu_runs(eng, ce.CE_KERNEL_NBODY_STEP, ce.ce_nbody_step_params(n, EPS2, dt, 0), [p_d, v_d], n, 2):
+        assert not np.isnan(x).any() and not np.isnan(v).any(), name
+        for i in at:
+            a, bound = bounds[i]
+            v64 = vel[i, :3].astype(np.float64)
+            slack = 2.0 ** -22 * (np.abs(v64) + np.abs(a * dt) + bound * dt)
+            assert np.all(np.abs(v[i, :3] - (v64 + a * dt)) <= bound * dt + slack), (name, i)
