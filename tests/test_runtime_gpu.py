@@ -137,3 +137,18 @@ def test_runtime_compile_error_leaves_engine_unbound(eng):
         eng.program_source("__device__ void f(uint64_t i, const ce_rt_args* a) { undeclared(i); }", "f", n_out=1)
     assert ei.value.status == ce.CE_E_INVALID and "undeclared" in str(ei.value)
     assert eng.run_status() == ce.CE_E_STATE
+
+
+def test_uneven_tiles_one_workgroup_each_over_many_rounds(eng):
+    """More than four rounds of resident workgroups, the GPU alone: the direct kernel
+    runs one workgroup per tile of 1024 work-items, swizzled over the XCDs in groups of
+    eight (8404 tiles: the last group is partial and keeps its order); twice, and the
+    same space as packages dealt by tickets."""
+    w, h, it = 4096, 2101, 64
+    ref = O.escape(w, h, X0, Y0, DX, DY, it)
+    eng.gpu_workgroups(0)
+    for sched in ("static", "static", "dynamic50"):
+        out, st, tr = run_escape(eng, w, h, it, w, ce.CE_DEV_GPU, sched, "dev")
+        assert (st.gpu_workgroups == w * h // 1024) == (sched == "static"), (sched, st.gpu_workgroups)
+        assert np.array_equal(out, ref), sched
+        check_trace(tr, h, 1)
