@@ -49,7 +49,6 @@ HBM_PEAK_GBS = 8000.0
 # instruction, which two or more waves fill (measured: 2.05 to 2.6 clocks per
 # instruction; one wave alone 5.1).
 FP32_PEAK_TFLOPS = 157.3
-FP32_NONPACKED_TFLOPS = 157.3
 # The same in vector instructions' lanes.
 VALU_ISSUE_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 # Escape-time flops and lane-ops are those of the definition (one step after
@@ -64,11 +63,13 @@ DEVICE_SOURCES = ("paper_1805_02755_amd/csrc/kernels.hip", "paper_1805_02755_amd
                   "paper_1805_02755_amd/csrc/device_divide.hpp", "paper_1805_02755_amd/csrc/binomial_call.hip",
                   "paper_1805_02755_amd/csrc/common.hpp", "paper_1805_02755_amd/csrc/sched_device.hpp",
                   "paper_1805_02755_amd/csrc/rt_tile.hpp")
+BATCH_SOURCES = DEVICE_SOURCES + ("paper_1805_02755_amd/csrc/dealing.hpp", "paper_1805_02755_amd/csrc/batch.hpp",
+                                  "paper_1805_02755_amd/csrc/batch_kernels.hip")
 
 
-def measured(name):
-    """A committed counter summary (profiles/NAME, JSON) if the device sources
-    it was taken from are unchanged, else None."""
+def measured(name, sources=DEVICE_SOURCES):
+    """A committed counter summary (profiles/NAME, JSON) if it was taken from
+    these device sources as they are now, else None."""
     import hashlib
     path = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(path):
@@ -76,7 +77,7 @@ def measured(name):
     with open(path) as f:
         rec = json.load(f)
     h = hashlib.sha256()
-    for src in rec.get("device_sources", DEVICE_SOURCES):
+    for src in sources:
         with open(os.path.join(ROOT, src), "rb") as f:
             h.update(f.read())
     if h.hexdigest() != rec.get("device_source_sha256"):
@@ -533,16 +534,15 @@ def escape_iterations(out_u32, np):
     return used, used / issued if issued else 1.0
 
 
-def alu_roofline(flops, lane_ops, kern_ms, kernel, counters_name=None):
+def alu_roofline(flops, lane_ops, kern_ms, kernel, counters_name=None, sources=DEVICE_SOURCES):
     achieved = flops / (kern_ms * 1e-3) / 1e12
     r = {"bound": "alu", "achieved": achieved, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-         "frac": achieved / FP32_PEAK_TFLOPS, "frac_of_nonpacked_peak": achieved / FP32_NONPACKED_TFLOPS,
-         "traffic": None, "kernel": kernel, "kernel_ms": kern_ms,
+         "frac": achieved / FP32_PEAK_TFLOPS, "traffic": None, "kernel": kernel, "kernel_ms": kern_ms,
          "issue": {"lane_ops": lane_ops, "achieved_T_lane_ops_per_s": lane_ops / (kern_ms * 1e-3) / 1e12,
                    "peak_T_lane_ops_per_s": VALU_ISSUE_TOPS,
                    "frac": lane_ops / (kern_ms * 1e-3) / 1e12 / VALU_ISSUE_TOPS}}
     if counters_name:
-        rec = measured(counters_name)
+        rec = measured(counters_name, sources)
         r["counters"] = {k: rec[k] for k in ("valu_busy", "valu_utilization", "valu_insts_per_dispatch",
                                              "valu_issue_frac_from_counts", "fp32_arith_issue_frac",
                                              "fp32_tflops_from_counts", "kernel_us_median_trace")
@@ -859,7 +859,7 @@ def bench_escape_roofline(args, ce, synth, torch, np, stream):
     assert torch.equal(out, ref)
     eng.close()
     iters, eff = escape_iterations(out.cpu().numpy().view(np.uint32), np)
-    r = alu_roofline(8.0 * iters, 8.0 * iters, med(kg), "k_persistent<EscapeTile>", "escape_8192_4096_valu.json")
+    r = alu_roofline(8.0 * iters, 8.0 * iters, med(kg), "k_sweep_escape", "escape_8192_4096_valu.json")
     r.update({"iterations": iters, "lane_efficiency": eff, "flops_per_iteration": 8, "counted": ESCAPE_COUNTED})
     rb = alu_roofline(8.0 * iters, 8.0 * iters, med(kb), "k_bare<EscapeTile>")
     res = {"metric": METRIC, "value": w * h / (med(kg) * 1e-3), "unit": "work-items/s", "n_gpus": 1, "steps": K,
@@ -1113,7 +1113,7 @@ def bench_binomial(args, ce, synth, torch, np, stream):
         "config": {"workload": "binomial options: 16777216 European calls, 254 steps, 4194304 work-groups of 255, "
                                "out pattern 1:255", "scheduler": "hguided", "devices": "gpu+host",
                    "residency": "device", "options_per_s": 4 * n_groups * K / T_total},
-        "roofline": alu_roofline(flops, lane_ops, med(kern_ms), "k_persistent<BinomialTile>",
+        "roofline": alu_roofline(flops, lane_ops, med(kern_ms), "k_persistent<BinomialCallTile>",
                                  "binomial_4194304x254_valu.json"),
         "cpu_baseline": cpu_base,
         "coexec": {
@@ -1191,7 +1191,7 @@ def bench_batch(args, ce, synth, torch, np, stream):
                    "form": "one persistent hipGraph launch", "tile_rows": chosen[0], "tile_cols": chosen[1],
                    "package_tiles": chosen[2]},
         "roofline": dict(alu_roofline(8.0 * iters, 8.0 * iters, med(kern), "k_batch_escape",
-                                      "batch_escape_256jobs_valu.json"), iterations=iters, counted=ESCAPE_COUNTED),
+                                      "batch_escape_256jobs_valu.json", BATCH_SOURCES), iterations=iters, counted=ESCAPE_COUNTED),
         "cpu_baseline": cpu_base,
         "batch": {"separate_launch_ms": med(t_sep) * 1e3, "separate_gpu_ms": med(g_sep),
                   "graph_launch_ms": med(per_run) * 1e3, "graph_gpu_ms": med(kern),
