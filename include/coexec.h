@@ -334,13 +334,14 @@ ce_status ce_engine_wait_bounds(ce_engine* e, double dispenser_s, double gather_
  * index space, R resident workgroups (occupancy x compute units) and C
  * compute units, the largest g <= min(T, R) that minimises
  * ceil(T / g) * ceil(g / C), the tiles run by the busiest compute unit
- * (whole rounds, spread evenly over the CUs); except that a run whose GPU
- * share is one package (the direct kernel) of equal-cost tiles with at
- * least 4 R tiles, or of escape-time or runtime-payload tiles with more
- * than 4 R, and at most 65536 tiles, gets one workgroup per tile, dealt by
- * the hardware as a plain launch is (runtime tiles swizzled over the XCDs; of
- * escape-time the first 2 R or 4 R share the pixels out and the rest leave at
- * once), and one of escape-time otherwise R, 2 R or 4 R, T at most.
+ * (whole rounds, spread evenly over the CUs), for n-body min(T, R) itself;
+ * except that a run whose GPU share is one package (the direct kernel) gets one
+ * workgroup per tile, dealt by the hardware as a plain launch is, where it
+ * has at most 65536 tiles and at least 4 R of equal cost (n-body: R), or more
+ * than 4 R of escape-time or of a runtime payload (runtime tiles swizzled over
+ * the XCDs; of escape-time the first 2 R or 4 R share the pixels out and the
+ * rest leave at once). Escape-time's share in one package otherwise gets R, 2 R
+ * or 4 R, T at most.
  * A caller's value is used as
  * given (it may exceed what fits on the GPU at once: the dispenser's
  * waits do not depend on every workgroup being resident), plus the gather
