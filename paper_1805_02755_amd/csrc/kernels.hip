@@ -56,7 +56,6 @@ struct SweepArgs {
 __global__ __launch_bounds__(kBlockThreads, EscapeTile::kMinBlocksPerCu) void k_sweep_escape(EscapeTile pay, DirectArgs d,
                                                                                             SweepArgs s) {
   __shared__ uint32_t next;
-  if (blockIdx.x >= d.sweepers) return;
   const bool first = threadIdx.x == 0;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
   if (first) {
@@ -68,7 +67,8 @@ __global__ __launch_bounds__(kBlockThreads, EscapeTile::kMinBlocksPerCu) void k_
     }
   }
   __syncthreads();
-  for (uint32_t i = w;;) {
+  const bool sweeps = blockIdx.x < s.round.d;
+  for (uint32_t i = w; sweeps;) {
     const uint32_t base = i * s.round.d;
     if (base >= s.blocks) break;
     uint32_t place, bx;
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kBlockThreads, EscapeTile::kMinBlocksPerCu) void k_
     i = __builtin_amdgcn_readfirstlane(taken);
   }
   __syncthreads();
-  if (first) sys_store(&d.wg_end[blockIdx.x], now_tick());
+  if (first && sweeps) sys_store(&d.wg_end[blockIdx.x], now_tick());
 }
 
 // N-body tiles of 64 that do not fill the GPU: eight waves per group of 64 bodies
