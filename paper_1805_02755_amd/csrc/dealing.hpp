@@ -39,7 +39,8 @@ constexpr uint32_t kDealBankWords = 16;  // a counter's own 128 bytes
 constexpr size_t kDealCounterBytes = (size_t)kDealBanks * kDealBankWords * sizeof(uint64_t);
 
 struct Deal {
-  uint64_t pieces, all_parts;   // the last piece may be short
+  uint64_t whole;               // pieces of `parts` parts
+  uint32_t rest;                // parts of the one after them
   uint32_t banks;
   Divisor groups;               // workgroups of a bank
   Divisor parts;                // waves' parts of a piece
@@ -50,10 +51,10 @@ struct Deal {
   uint64_t* counters;           // kDealCounterBytes, zero: a bank's claims after level 0, and its workgroups that left
 
   __host__ Deal(uint64_t n_parts, uint32_t workgroups, uint32_t parts_per_piece, uint64_t* c)
-      : pieces(n_parts / parts_per_piece + (n_parts % parts_per_piece != 0)), all_parts(n_parts), banks(workgroups % kDealBanks ? 1u : kDealBanks), groups(workgroups / banks), parts(parts_per_piece),
+      : whole(n_parts / parts_per_piece), rest((uint32_t)(n_parts % parts_per_piece)), banks(workgroups % kDealBanks ? 1u : kDealBanks), groups(workgroups / banks), parts(parts_per_piece),
         turn((uint32_t)(groups.d * 5ull / 8) | 1u), levels(0), counters(c) {
     const uint32_t least = (kDealLeastParts + parts_per_piece - 1) / parts_per_piece;
-    const uint64_t all = pieces / banks + (pieces % banks != 0);
+    const uint64_t pieces = whole + (rest != 0), all = pieces / banks + (pieces % banks != 0);
     // an eighth, or as little more as the table has room for (2^14 pieces per workgroup)
     for (uint64_t share = 8; share >= 1; --share) {
       uint64_t at = 0;
@@ -114,7 +115,7 @@ __device__ __forceinline__ bool deal_next(const Deal& d, DealState& s, uint64_t*
     place += rotated;
     const uint64_t own = d.start[level] + (uint64_t)j * d.groups.d + (place < d.groups.d ? place : place - d.groups.d);
     *piece = own * d.banks + (blockIdx.x & (d.banks - 1));
-    if (*piece + 1 < d.pieces || *piece * d.parts.d + *part < d.all_parts) return true;
+    if (__builtin_expect(*piece < d.whole, 1) || (*piece == d.whole && *part < d.rest)) return true;
     // nothing left in this piece: on to the next (unless the claim is over), not
     // part by part, since a caller's piece may have millions
     if (first)
