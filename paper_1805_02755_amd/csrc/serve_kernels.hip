@@ -26,10 +26,14 @@ constexpr uint32_t kDescWords = sizeof(ServeDesc) / 8;
 // fewer instructions when the GPU is full. Strict, in us, groups and whole
 // granules for all jobs: 1 of 4,096 bodies 162 and 283, 16 302 and 452, 64 734 and
 // 758, 4 of 16,384 726 and 1385, 128 of 8,192 3968 and 3446, 64 of 20,000 11050
-// and 9630 (decided so 10646).
+// and 9630 (decided so 10646). A job of 32,768 bodies and more in groups would end
+// sooner on its own (65,536: 2.6 ms, 3.5 in whole granules) but hold every workgroup
+// meanwhile, where its whole granules leave most to the jobs beside it: the trace of
+// 2,000 jobs at half load had a median latency of 1.5 ms so, 0.8 in whole granules.
 // The groups' chunks are shorter than the engine's, which would leave the
 // kernel four workgroups per compute unit instead of five.
 constexpr uint64_t kServeGroupGranules = 1024;
+constexpr uint32_t kServeWholeBodies = 32768;
 constexpr uint32_t kServeNbodyChunk = 8;
 constexpr uint32_t kServeNbodyLds = sizeof(f32x4[2 * kNbodyWhole]);
 
@@ -225,7 +229,7 @@ void serve_plan(ServeDesc& d, uint64_t busy) {
       break;
     case CE_KERNEL_NBODY_ACC:
       d.granules = ceil_div(d.nb.n, kNbodyGranule);
-      d.form = busy + d.granules > kServeGroupGranules;
+      d.form = d.nb.n >= kServeWholeBodies || busy + d.granules > kServeGroupGranules;
       d.ntiles = d.form ? (uint32_t)d.granules : nbody_tiles(d.nb.n, 0, d.granules);
       break;
   }
