@@ -41,9 +41,16 @@ CE_HD uint32_t escape_block_bits(uint64_t rows, uint32_t least = 4) {
 // less where they straddle lines. In blocks of 16 x 4, 32 x 2 and 64 x 1, the GPU
 // alone: 4096^2, max_iter 256 1503, 1304, 1219 us; 4095 x 4097 1813, 1560, 1391;
 // 4096^2, 4000 1546, 1330, 1256; 1024^2, 256 116, 103, 98; 1920 x 1080, 2000 210,
-// 225, 205. Only where the longest orbits set the time it is slower (1920 x 1080,
-// 4000 246, 263, 274).
+// 225, 205. A row of 64 holds a wave for its longest orbit, though, so with deep
+// caps the rows are slower, and in small images sooner. Blocks of 16 x 4 and 64 x 1,
+// the GPU alone and (with the host, HGuided): max_iter 1000 1920 x 1080 200, 197;
+// 2000 210, 224 (257, 279); 4096 284, 276 (317, 359); 2560 x 2001, 4096 491, 411
+// (506, 531); 4096 x 2160, 4096 824, 705 (654, 630), 10000 938, 892, 30000 1239,
+// 1992; 4096^2, 4096 1545, 1275 (1191, 1056), 30000 2137, 2627.
 CE_HD uint32_t escape_least_bits(uint32_t w, bool host_memory) { return host_memory && w >= 32 ? (w >= 64 ? 6u : 5u) : 4u; }
+CE_HD uint32_t escape_least_bits(uint32_t w, uint32_t h, uint32_t max_iter, bool host_memory) {
+  return escape_least_bits(w, host_memory && max_iter <= ((uint64_t)w * h >= (1u << 23) ? 4096u : 1024u));
+}
 
 // Whether the GPU prices binomial calls one per lane (tiles of 64 groups)
 // rather than one group per wave (tiles of four): `groups` is the GPU's share

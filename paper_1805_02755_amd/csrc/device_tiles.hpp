@@ -30,10 +30,11 @@ struct EscapeTile {
   static constexpr bool kWavesAlone = true;  // a tile's parts need no barrier between them
   ce_escape_params p;
   uint32_t* out;
-  Divisor across;       // blocks of 16 x 4 side by side
+  Divisor across;       // the blocks side by side where they are 16 x 4
   uint32_t least_bits;  // of a block's columns
   __host__ __device__ EscapeTile(const ce_escape_params& params, uint32_t* o, bool host_memory)
-      : p(params), out(o), across(escape_blocks_across(params.w, 4)), least_bits(escape_least_bits(params.w, host_memory)) {}
+      : p(params), out(o), across(escape_blocks_across(params.w, 4)),
+        least_bits(escape_least_bits(params.w, params.h, params.max_iter, host_memory)) {}
   __device__ void load_constants() {}
   __host__ __device__ uint32_t ncb() const { return (uint32_t)ceil_div(p.w, kEscapeTileCols); }
   __host__ __device__ uint64_t granules() const { return p.h; }

@@ -1357,7 +1357,7 @@ struct ce_engine {
       const bool sweep = light_exit && gs.pre_only && kernel_id == CE_KERNEL_ESCAPE;
       if (sweep) {
         const uint64_t rows = gs.pre_g1 - gs.pre_g0;
-        const uint32_t bits = escape_block_bits(rows, escape_least_bits(esc.w, pcie_stream));
+        const uint32_t bits = escape_block_bits(rows, escape_least_bits(esc.w, esc.h, esc.max_iter, pcie_stream));
         const uint64_t blocks = escape_blocks_across(esc.w, bits) * escape_blocks_down(rows, bits);
         sweepers = grid_override ? grid : sweep_workers(gs.pre_nt, blocks, resident_wgs);
         const bool per_tile = gs.pre_nt > kDirectOneShotRounds * (uint64_t)resident_wgs && gs.pre_nt <= kFastExitMaxWgs;

@@ -275,7 +275,7 @@ hipError_t launch_direct(const KernelArgs& a, const DirectArgs& d, uint32_t grid
   const dim3 g(grid), b(kBlockThreads);
   switch (a.kernel_id) {
     case CE_KERNEL_ESCAPE: {
-      const uint32_t bits = escape_block_bits(d.g1 - d.g0, escape_least_bits(a.esc.w, a.host_memory));
+      const uint32_t bits = escape_block_bits(d.g1 - d.g0, escape_least_bits(a.esc.w, a.esc.h, a.esc.max_iter, a.host_memory));
       const uint64_t per_row = escape_blocks_across(a.esc.w, bits), blocks = per_row * escape_blocks_down(d.g1 - d.g0, bits);
       if (blocks >= (1ull << 30)) {
         hipLaunchKernelGGL(k_direct<EscapeTile>, g, b, 0, st, make_escape(a), d);

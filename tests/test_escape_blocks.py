@@ -73,3 +73,25 @@ def test_tiles_of_host_memory_suit_the_link(tmp_path):
         assert rows in (2, 4, 8, 16, 32)
         assert rows == 32 or tiles < 64
         assert rows == 2 or tiles >= 32
+
+
+DEEP_SRC = r"""
+#include <cstdio>
+#include "common.hpp"
+int main() {
+  const uint32_t calls[][3] = {{64, 64, 1}, {64, 64, 1024}, {64, 64, 1025}, {40, 64, 1024}, {20, 64, 1}, {4096, 2047, 1025},
+                               {4096, 2048, 1025}, {4096, 2048, 4096}, {4096, 2048, 4097}, {65536, 65536, 4096}};
+  for (auto& c : calls) printf("%u %u ", ce::escape_least_bits(c[0], c[1], c[2], true), ce::escape_least_bits(c[0], c[1], c[2], false));
+}
+"""
+
+
+def test_deep_caps_keep_square_blocks(tmp_path):
+    """A wave of 64 pixels in a row lasts as long as its longest orbit: into host
+    memory rows are taken up to max_iter 1024 only, 4096 from 2^23 pixels on."""
+    src = tmp_path / "deep.cpp"
+    src.write_text(DEEP_SRC)
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", str(tmp_path / "deep"), str(src)], check=True)
+    out = subprocess.run([str(tmp_path / "deep")], check=True, capture_output=True, text=True).stdout.split()
+    assert [int(x) for x in out[::2]] == [6, 6, 4, 5, 4, 4, 6, 6, 4, 6]
+    assert [int(x) for x in out[1::2]] == [4] * 10

@@ -88,3 +88,14 @@ def test_block_and_tile_shapes_pinned(eng, w, h):
         out, st, tr = run_payload(eng, ce.CE_KERNEL_BLUR5, ce.ce_blur5_params(w, h), [w, h], None, [img, wt], (h, w),
                                   np.float32, devs, sched, mode="pinned")
         assert np.array_equal(out.view(np.uint32), blurred.view(np.uint32)), (sched, diff_report(out, blurred, tr))
+
+
+@pytest.mark.parametrize("cap", [1024, 1025])
+def test_escape_block_shapes_by_cap_pinned(eng, cap):
+    w, h = 515, 130
+    p = synth.escape_region(w, h, -2.0, 0.6, -1.2, 1.2, cap)
+    ref = O.escape(p.w, p.h, *[float(v) for v in p.as_f32()], p.max_iter)
+    for devs, sched in ((ce.CE_DEV_GPU, "static"), (ce.CE_DEV_GPU, "dynamic"), (BOTH, "hguided")):
+        out, st, tr = run_payload(eng, ce.CE_KERNEL_ESCAPE, escape_params(p), [w, h], None, [], (h, w), np.uint32,
+                                  devs, sched, mode="pinned")
+        assert np.array_equal(out, ref), (sched, diff_report(out, ref, tr))
