@@ -334,7 +334,8 @@ ce_status ce_engine_wait_bounds(ce_engine* e, double dispenser_s, double gather_
  * index space, R resident workgroups (occupancy x compute units) and C
  * compute units, the largest g <= min(T, R) that minimises
  * ceil(T / g) * ceil(g / C), the tiles run by the busiest compute unit
- * (whole rounds, spread evenly over the CUs), for n-body min(T, R) itself;
+ * (whole rounds, spread evenly over the CUs), for n-body, and for escape-time
+ * from 2 R tiles on, min(T, R) itself;
  * except that a run whose GPU share is one package (the direct kernel) gets one
  * workgroup per tile, dealt by the hardware as a plain launch is, where it
  * has at most 65536 tiles and at least 4 R of equal cost (n-body: R), or more

@@ -1156,9 +1156,16 @@ struct ce_engine {
         // bound by issue, which several workgroups of a compute unit fill and
         // one does not, so whole rounds of fewer workgroups lose (77,578
         // bodies, 1213 tiles: five rounds of 256 took 5.0 ms, one workgroup
-        // per tile 2.8).
-        grid = (uint32_t)(is_nbody() ? std::min(all_tiles, r) : balanced_grid(all_tiles, r, (uint64_t)std::max(1, n_cu))) +
-               gather_wgs;
+        // per tile 2.8). Escape-time likewise from two rounds on (1920 x 1080
+        // is 4320 tiles, whole rounds of 256 or two and a bit of 2048):
+        // HGuided, the GPU alone, max_iter 16, 256, 2000 77, 87, 142 us
+        // against 45, 38, 105, Dynamic in packages of 16 rows 206, 220, 212
+        // against 61, 66, 108; 3000 x 2001, HGuided 129, 216, 288 against 52,
+        // 67, 146. In fewer rounds whole ones are as good or better (1000 x
+        // 1500, 16 31 against 33; 1280 x 720, 4000 107 against 132).
+        const bool all_resident = is_nbody() || (kernel_id == CE_KERNEL_ESCAPE && all_tiles >= 2 * r);
+        grid = (uint32_t)(all_resident ? std::min(all_tiles, r)
+                                       : balanced_grid(all_tiles, r, (uint64_t)std::max(1, n_cu))) + gather_wgs;
       }
       if (grid <= gather_wgs) grid = gather_wgs + 1;
     }
@@ -1259,9 +1266,10 @@ struct ce_engine {
       //   2048^2,  cap 64       48   73   54  172    86   92   85  162    84   91   86  165
       //   4096^2,  64          122  233  120  229   156  195  151  196   146  206  153  196
       //   8192^2,  64          407  792  364  558   312  606  303  329   406  640  402  446
-      //   3000 x 2001, 64      139  268  127  312   191  354  152  179   205  365  172  205
+      //   3000 x 2001, 64       57  113   64  173   109  126  109  158   109  131  111  156
       //   8192^2,  256         612  854  485  754   369  611  364  409   441  664  442  481
-      //   1920 x 1080, 1000    140  203  200  276   153  175  168  251   106  129  125  162
+      //   1920 x 1080, 1000     65   72   73  131    80   77   82  130    82   80   81  129
+      //   1920 x 1080, 4000    183  182  192  231   139  160  161  223   138  147  153  195
       //   4096^2,  1000        351  315  274  300   210  299  230  306   180  241  195  242
       //   8192^2,  4000       2322 1851 2108 3436  1154 1551 1126 1276   807  972  835  979
       // Deep: the blocks that run to a deep cap (some tens of microseconds each)

@@ -179,3 +179,32 @@ def test_many_tiles_and_many_bands(w, h, cap):
                 torch.cuda.synchronize()
                 eng.run()
                 assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), sched
+
+
+@pytest.mark.parametrize("w,h", [(512, 4095), (512, 4096), (515, 2049), (1920, 1080)])
+def test_grid_of_packages_around_two_rounds(w, h):
+    """In packages, escape-time takes whole rounds of tiles below two rounds of
+    resident workgroups (eight per compute unit) and all of them from there on."""
+    prm = ce.ce_escape_params(w, h, -2.0, -1.5, float(np.float32(3.0 / w)), float(np.float32(3.0 / h)), 300)
+    ref = O.escape(w, h, -2.0, -1.5, prm.dx, prm.dy, 300)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    resident, tiles = 8 * cus, h * -(-w // 512)
+    out = torch.empty((h, w), dtype=torch.int32, device="cuda:0")
+    with ce.Engine() as eng:
+        for devs in (ce.CE_DEV_GPU, ce.CE_DEV_GPU | ce.CE_DEV_HOST):
+            eng.use(devs, 0, 0 if devs == ce.CE_DEV_GPU else 4)
+            eng.work_items([w, h])
+            eng.program_kernel(ce.CE_KERNEL_ESCAPE, prm)
+            eng.program_out(0, dev=out, nbytes=out.numel() * 4)
+            for sched in (dict(kind=ce.CE_SCHED_HGUIDED, k=2, power=[9, 1][:1 if devs == ce.CE_DEV_GPU else 2]),
+                          dict(kind=ce.CE_SCHED_DYNAMIC, package_granules=16)):
+                eng.scheduler(**sched)
+                out.fill_(-1)
+                torch.cuda.synchronize()
+                eng.run()
+                assert np.array_equal(out.cpu().numpy().view(np.uint32), ref), sched
+                g = eng.stats().gpu_workgroups
+                if tiles >= 2 * resident:
+                    assert g == resident, (g, tiles)
+                else:
+                    assert -(-tiles // g) * -(-g // cus) == -(-tiles // cus), (g, tiles)
